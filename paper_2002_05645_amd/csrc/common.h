@@ -170,6 +170,10 @@ __device__ __forceinline__ void gelu_and_grad_fast_f(float u, float& gelu, float
 template <typename E> __device__ __forceinline__ float gelu_epi(float u) { return gelu_fast_f(u); }
 template <typename E> __device__ __forceinline__ float gelu_grad_epi(float u) { return gelu_grad_fast_f(u); }
 template <typename E> __device__ __forceinline__ void gelu_and_grad_epi(float u, float& g, float& d) { gelu_and_grad_fast_f(u, g, d); }
+// ... and of the fp32 ones: the exact forms
+template <> __device__ __forceinline__ float gelu_epi<float>(float u) { return gelu_f(u); }
+template <> __device__ __forceinline__ float gelu_grad_epi<float>(float u) { return gelu_grad_f(u); }
+template <> __device__ __forceinline__ void gelu_and_grad_epi<float>(float u, float& g, float& d) { g = gelu_f(u); d = gelu_grad_f(u); }
 
 // Epilogue flags of the GEMM kernels.
 // EPI_COLSUM: also leave the column sums of the stored values in GemmArgs::colsum (a bias gradient that would

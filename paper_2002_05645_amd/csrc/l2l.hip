@@ -15,6 +15,7 @@
 
 #include "../../include/l2l.h"
 #include "gemm.h"
+#include "gemm_f32.h"
 #include "gemm_variants.h"
 #include "attention.h"
 #include "rowwise.h"
@@ -357,6 +358,75 @@ void launch_plain(const GemmArgs& g, hipStream_t s) {
   hipLaunchKernelGGL((gemm_plain_kernel<T, TC>), grid, dim3(256), 0, s, g);
 }
 
+// ---- fp32 operands -------------------------------------------------------------------------------
+// what gemm_f32_kernel can address: 16-byte chunks, and panels below 2 GiB whose K-strided loads do not wrap (they run up
+// to two k-tiles past the end)
+bool f32_mfma_ok(const GemmArgs& g) {
+  const auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  if (!al16(g.A) || !al16(g.B) || g.lda % 4 || g.ldb % 4) return false;
+  if (g.a_zo % 4 || g.a_zi % 4 || g.b_zo % 4 || g.b_zi % 4) return false;
+  const long long m4 = up(g.M, 4), n4 = up(g.N, 4), k4 = up(g.K, 4);
+  if (g.lda < (g.a_kc ? k4 : m4) || g.ldb < (g.b_kc ? k4 : n4)) return false;
+  const long long lim = (1LL << 31) - 1;
+  const long long ea = g.a_kc ? (long long)(g.M + 63) * g.lda + k4 : (long long)(g.K + 64) * g.lda + m4;
+  const long long eb = g.b_kc ? (long long)(g.N + 63) * g.ldb + k4 : (long long)(g.K + 64) * g.ldb + n4;
+  return ea * 4 <= lim && eb * 4 <= lim;
+}
+
+// whether the K splits of a launch may go through a workspace and split_epilogue_kernel (any epilogue but column sums)
+bool split_epilogue_ok(const GemmArgs& g) {
+  return g.nbatch == 1 && !(g.epi & EPI_COLSUM) && gemm_vec_ok(g, g.epi, g.C);
+}
+
+// K splits of an fp32 launch: the number with the shortest estimated time.  A compute unit's matrix cores take 0.6 us for a
+// k-tile of 32 (what 100 TFLOP/s over the chip come to); a workgroup alone on its unit waits for its loads, which makes
+// that 0.9 us until two share a unit; splits cost a second launch and the traffic of the partial sums.
+int pick_f32_splits(const GemmArgs& g, size_t ws_elems) {
+  const int nk = std::max(1, (g.K + 31) / 32);
+  const long long tiles = (long long)((g.M + F32_TILE - 1) / F32_TILE) * ((g.N + F32_TILE - 1) / F32_TILE) * g.nbatch;
+  int best_s = 1;
+  double best = 1e300;
+  for (int s = 1; s <= (split_epilogue_ok(g) ? std::min(32, std::max(1, nk / 2)) : 1); ++s) {
+    if (s > 1 && (size_t)s * g.M * g.N > ws_elems) break;
+    const int kt = (nk + s - 1) / s;
+    if (s > 1 && (nk + kt - 1) / kt != s) continue;   // an empty split
+    const double per_cu = std::ceil((double)tiles * s / 256.0);
+    double us = kt * std::max(per_cu * 0.6, std::ceil(per_cu / 4.0) * 0.9) + 2.0;
+    if (s > 1) us += 3.0 + (double)s * g.M * g.N * 8.0 / 4.0e6;
+    if (us < best) { best = us; best_s = s; }
+  }
+  return best_s;
+}
+
+void launch_f32(const GemmArgs& g, hipStream_t s, int splits) {
+  const auto go = [&](auto akc, auto bkc) {
+    constexpr bool AKC = decltype(akc)::value, BKC = decltype(bkc)::value;
+    constexpr int LDS = 2 * (F32Tile<F32_TILE, AKC>::FLOATS + F32Tile<F32_TILE, BKC>::FLOATS) * 4;
+    static_assert(LDS <= 64 * 1024, "within what a launch may take without asking");
+    const int tiles = ((g.M + F32_TILE - 1) / F32_TILE) * ((g.N + F32_TILE - 1) / F32_TILE);
+    hipLaunchKernelGGL((gemm_f32_kernel<AKC, BKC>), dim3(tiles, splits, g.nbatch), dim3(256), LDS, s, g);
+  };
+  if (g.a_kc && g.b_kc) go(std::true_type{}, std::true_type{});
+  else if (g.a_kc) go(std::true_type{}, std::false_type{});
+  else if (g.b_kc) go(std::false_type{}, std::true_type{});
+  else go(std::false_type{}, std::false_type{});
+}
+
+// adds the K splits' partial results in `ws` up and applies the launch's epilogue
+template <typename E, typename TC>
+void launch_split_epilogue(const GemmArgs& g, const float* ws, int splits, hipStream_t s) {
+  const unsigned blocks = (unsigned)std::min<long long>(((long long)g.M * (g.N / 8) + 255) / 256, 4096);
+  hipLaunchKernelGGL((split_epilogue_kernel<E, TC>), dim3(blocks), dim3(256), 0, s, ws, splits, g);
+}
+
+void gemm_f32(const GemmArgs& g, hipStream_t s, float* ws, size_t ws_elems) {
+  const int splits = pick_f32_splits(g, ws ? ws_elems : 0);
+  GemmArgs p = g;
+  if (splits > 1) { p.C = ws; p.ldc = g.N; p.split_stride = (long long)g.M * g.N; p.epi = 0; }
+  launch_f32(p, s, splits);
+  if (splits > 1) launch_split_epilogue<float, float>(g, ws, splits, s);
+}
+
 // tile variant and split-K factor for one launch
 void pick_tile(const GemmArgs& g, bool out_f32, int* variant, int* splits) {
   int v = 0;
@@ -379,6 +449,14 @@ void pick_tile(const GemmArgs& g, bool out_f32, int* variant, int* splits) {
     *splits = (int)std::max<long long>(1, std::min<long long>(want, 64));
   }
   *variant = v;
+}
+
+// the variant that runs a launch for which v was chosen or asked for: the direct-to-LDS kernel is not built for A K-strided
+// with B K-contiguous, and with tiles below 128 rows for K-contiguous operands only
+int variant_for_layout(int v, const GemmArgs& g) {
+  if (!kTiles[v].direct || (g.a_kc && g.b_kc)) return v;
+  if (kTiles[v].bm < 128) return 0;
+  return !g.a_kc && g.b_kc ? 3 : v;
 }
 
 // whether gemm() will run this launch on the direct-to-LDS kernel, the one that honours EPI_COLSUM; otherwise the
@@ -446,7 +524,7 @@ int gemm(l2l_ctx* c, int dtype, bool out_f32, const GemmArgs& g, int impl = 0, i
       int v, splits;
       pick_tile(g, out_f32, &v, &splits);
       if (impl >= 100) v = impl - 100;
-      if (kTiles[v].direct && !g.a_kc && g.b_kc) v = 3;   // no direct-to-LDS kernel for A K-strided with B K-contiguous
+      v = variant_for_layout(v, g);
       if (c->force_splits > 0 && out_f32 && g.epi == EPI_ACCUM) splits = c->force_splits;
       GemmArgs gr = g;
       gr.resident = c->resident_cus;
@@ -464,6 +542,8 @@ int gemm(l2l_ctx* c, int dtype, bool out_f32, const GemmArgs& g, int impl = 0, i
     } else if (dtype == L2L_FP16) {
       if (out_f32) launch_plain<fp16, float>(g, c->cs);
       else launch_plain<fp16, fp16>(g, c->cs);
+    } else if (impl == 0 && f32_mfma_ok(g)) {
+      gemm_f32(g, c->cs, c->split_ws, c->split_ws_elems);
     } else {
       launch_plain<float, float>(g, c->cs);
     }
@@ -1156,6 +1236,22 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
     }
     if (const char* e = getenv("L2L_SPLIT_WS_MB")) need = (size_t)atoll(e) << 18;   // tuning: room for other split factors
     if (need > 0 && need * 4 <= (size_t)256 << 20) {
+      c->split_ws_elems = need;
+      L2L_TRY(dev_alloc(c, (void**)&c->split_ws, need * 4));
+    }
+  }
+  if (!is16(cfg->dtype)) {   // fp32: the largest room that the K splits of the layer's GEMMs ask for, within 32 MB
+    constexpr size_t kMost = (size_t)8 << 20;
+    size_t need = 0;
+    const int h = cfg->hidden, f = cfg->ffn, m = (int)Mg;
+    const int shapes[][3] = {{m, 3 * h, h}, {m, h, h}, {m, f, h}, {m, h, f}, {m, h, 3 * h}, {h, 3 * h, m}, {h, h, m}, {h, f, m}, {f, h, m}};
+    for (const auto& s : shapes) {
+      GemmArgs g = gemm_args(s[0], s[1], s[2], nullptr, s[2], 1, nullptr, s[2], 1, nullptr, s[1]);
+      const int splits = pick_f32_splits(g, kMost);
+      if (splits > 1) need = std::max(need, (size_t)splits * s[0] * s[1]);
+    }
+    if (const char* e = getenv("L2L_SPLIT_WS_MB")) need = (size_t)atoll(e) << 18;
+    if (need > 0) {
       c->split_ws_elems = need;
       L2L_TRY(dev_alloc(c, (void**)&c->split_ws, need * 4));
     }
@@ -1871,7 +1967,7 @@ int l2l_op_gemm_accum_noalloc(void* stream, int in_dtype, int a_kc, int b_kc, in
   if ((g.M + 63) / 64 > 65535) return noalloc_fail(L2L_E_ARG, "l2l_op_gemm_accum_noalloc: grid too large");
   int v, splits;
   pick_tile(g, true, &v, &splits);
-  if (kTiles[v].direct && !g.a_kc && g.b_kc) v = 3;
+  v = variant_for_layout(v, g);
   float* ws = nullptr;
   int cus = 0;
   L2L_TRY(noalloc_scratch(&ws, &cus));

@@ -742,6 +742,28 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* part, int s
   }
 }
 
+// C = epi(alpha-scaled sum of the splits' partial results), for the splits of a GEMM with any epilogue: what the GEMM kernel's
+// own epilogue would have done, on 8 columns per thread (gemm_vec_ok holds).  part: `splits` dense [M, N] slices, of which
+// the first *m_dev rows are written where the GEMM has a device-side row bound.
+template <typename E, typename TC>
+__global__ __launch_bounds__(256) void split_epilogue_kernel(const float* part, int splits, GemmArgs g) {
+  const int M = g.m_dev ? min(g.M, *g.m_dev) : g.M, n8 = g.N / 8;
+  const long long slice = (long long)g.M * g.N, total = (long long)M * n8;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+    const long long m = i / n8;
+    const int n = (int)(i - m * n8) * 8;
+    const float* p = part + m * g.N + n;
+    float v[8], t[8];
+    load8(p, v);
+    for (int k = 1; k < splits; ++k) {
+      load8(p + k * slice, t);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += t[e];
+    }
+    epilogue8<E, TC>(g, (TC*)g.C, m, n, v, false);
+  }
+}
+
 // p[i] = v for i < n (a kernel rather than a memset so that callers can capture it in a graph).
 // 16-byte stores over the aligned body, dwords for the tail.
 __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* p, uint32_t v, long long n) {

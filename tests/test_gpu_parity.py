@@ -126,6 +126,22 @@ def test_gemm_every_tile_variant(ctx, variant):
         ctx.op_gemm(P.L2L_BF16, False, 1, 0, 64, 64, 64, x, 64, x, 64, x, 64, impl=100 + 9)   # one past the last variant
 
 
+@pytest.mark.parametrize("a_kc,b_kc", [(1, 0), (1, 1), (0, 0), (0, 1)])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (63, 72, 31), (64, 64, 2048), (65, 136, 4100), (129, 258, 40), (1040, 1032, 33), (200, 136, 613)])
+def test_gemm_fp32_matrix_core_kernel(monkeypatch, M, N, K, a_kc, b_kc):
+    # fp32 operands through the library's choice of kernel: edges of the 64-row tiles, k-tiles of 32 with tails
+    # (K no multiple of 4 too), K splits through the workspace (few tiles, long K; pad 8) and what cannot be split (pad 3)
+    monkeypatch.setenv("L2L_SPLIT_WS_MB", "32")
+    c = P.Context(P.make_config(64, 2, 128, 16, 2, 2, "fp32", 1e-5, 0))
+    try:
+        assert _gemm_case(c, "fp32", 0, a_kc, b_kc, M, N, K, seed=M) < 2e-6
+        assert _gemm_case(c, "fp32", 0, a_kc, b_kc, M, N, K, bias=True, resid=True, alpha=0.5, seed=M, pad=8) < 2e-6
+        assert _gemm_case(c, "fp32", 0, a_kc, b_kc, M, N, K, bias=True, gelu=True, alpha=0.1, seed=M, pad=8) < 2e-6
+        assert _gemm_case(c, "fp32", 0, a_kc, b_kc, M, N, K, accumulate=True, seed=M, pad=8) < 2e-6
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("workspace_mb", [0, 64])
 def test_gemm_split_k_through_workspace_and_with_atomics(monkeypatch, workspace_mb):
     # an accumulating fp32 GEMM with few tiles and a long K is split over K; the splits either store partial tiles in a

@@ -555,7 +555,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   const float alpha = EPI >= 0 ? 1.0f : g.alpha;   // the launcher sends only alpha = 1 to the kernels with compiled-in flags
   constexpr int NWM = BM / WM, NWN = BN / WN, NT = NWM * NWN * 64;
   constexpr int FM = WM / 32, FN = WN / 32, KK = BK / 16;
-  static_assert(WM % 64 == 0 && WN % 64 == 0, "wave tiles start on multiples of 64 rows / columns");
+  static_assert((WM % 64 == 0 && WN % 64 == 0) || (AKC && BKC), "K-strided images are swizzled in groups of 128 rows / columns");
   using DA = DirectLoader<BM, NT, AKC>;
   using DB = DirectLoader<BN, NT, BKC>;
   constexpr int STAGE = DA::BYTES + DB::BYTES;

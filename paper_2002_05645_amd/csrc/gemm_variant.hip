@@ -44,7 +44,9 @@ void launch_direct_one(const GemmArgs& g, hipStream_t s, int splits) {
     return true;
   }();
   (void)once;
-  const int num_cus = g.resident / 8 * 8;   // a multiple of the 8 XCDs keeps each resident workgroup's tiles on its own XCD's range
+  // (the tiles of which two or four share a compute unit are not made resident: one workgroup per unit would wait for
+  // its own loads; 32768 x 4096 x 1024 on 128 x 128 tiles 450 us resident, 322 us with a workgroup per tile)
+  const int num_cus = BM == 256 ? g.resident / 8 * 8 : 0;   // a multiple of the 8 XCDs keeps each resident workgroup's tiles on its own XCD's range
   const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   // more tiles than CUs: one resident workgroup per CU walks the tile order (the kernel's loop)
   const int gx = (num_cus > 0 && splits == 1 && g.nbatch == 1 && tiles > num_cus) ? num_cus : tiles;
@@ -56,10 +58,10 @@ void launch_direct_one(const GemmArgs& g, hipStream_t s, int splits) {
 // K-contiguous (forward with transposed weights, dX) and both K-strided (dW)
 template <int BM, int BN, int WM, int WN, typename TC, typename E>
 void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
-  // The 256 x 256 tile with 16-bit output and both operands K-contiguous carries the layer's forward, recompute and
-  // dX GEMMs: their eight epilogues get kernels with the flags compiled in (a third off the epilogue's time); any
-  // other combination runs the kernel that reads the flags at run time.
-  if constexpr (BM == 256 && BN == 256 && sizeof(TC) == 2) {
+  // 16-bit output and both operands K-contiguous: the layer's forward, recompute and dX GEMMs.  Their eight epilogues
+  // get kernels with the flags compiled in (a third off the epilogue's time); any other combination runs the kernel
+  // that reads the flags at run time.
+  if constexpr (sizeof(TC) == 2) {
     if (g.a_kc && g.b_kc && g.alpha == 1.0f) {
       switch (g.epi) {
 #define L2L_EPI_CASE(e) case (e): launch_direct_one<BM, BN, WM, WN, true, true, TC, E, (e)>(g, s, splits); return;
@@ -76,9 +78,13 @@ void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
       }
     }
   }
-  if (g.a_kc && g.b_kc) launch_direct_one<BM, BN, WM, WN, true, true, TC, E>(g, s, splits);
-  else if (g.a_kc) launch_direct_one<BM, BN, WM, WN, true, false, TC, E>(g, s, splits);
-  else launch_direct_one<BM, BN, WM, WN, false, false, TC, E>(g, s, splits);
+  if constexpr (BM < 128) {   // built for K-contiguous operands only: callers see to it
+    launch_direct_one<BM, BN, WM, WN, true, true, TC, E>(g, s, splits);
+  } else {
+    if (g.a_kc && g.b_kc) launch_direct_one<BM, BN, WM, WN, true, true, TC, E>(g, s, splits);
+    else if (g.a_kc) launch_direct_one<BM, BN, WM, WN, true, false, TC, E>(g, s, splits);
+    else launch_direct_one<BM, BN, WM, WN, false, false, TC, E>(g, s, splits);
+  }
 }
 
 struct TileCfg { int bm, bn, bk, wm, wn, direct; };

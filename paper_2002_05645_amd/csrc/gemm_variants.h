@@ -1,5 +1,5 @@
 // Tile variants of the bf16 MFMA GEMM: X(index, BM, BN, BK, WM, WN, direct).  direct = 1: the kernel
-// whose global loads go straight into LDS (both operands K-contiguous only).  Each variant is compiled
+// whose global loads go straight into LDS (the 64 x 64 tile: both operands K-contiguous only).  Each variant is compiled
 // in its own translation unit (gemm_variant.hip with -DL2L_VARIANT=index) so that the build runs in parallel.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -11,7 +11,7 @@
   X(2, 256, 128, 64, 64, 64, 0) \
   X(3, 256, 256, 64, 128, 64, 0) \
   X(4, 256, 256, 64, 64, 128, 0) \
-  X(5, 128, 256, 64, 64, 64, 0) \
+  X(5, 64, 64, 64, 32, 32, 1) \
   X(6, 256, 256, 64, 128, 64, 1) \
   X(7, 128, 128, 64, 64, 64, 1) \
   X(8, 256, 128, 64, 64, 64, 1)

@@ -427,7 +427,8 @@ void gemm_f32(const GemmArgs& g, hipStream_t s, float* ws, size_t ws_elems) {
   if (splits > 1) launch_split_epilogue<float, float>(g, ws, splits, s);
 }
 
-// tile variant and split-K factor for one launch
+// Tile variant and split-K factor for one launch, by size alone: the rule where the K splits add with atomics, where they
+// have a fixed scratch array, and for the layouts that choose_tile has no timings of.
 void pick_tile(const GemmArgs& g, bool out_f32, int* variant, int* splits) {
   int v = 0;
   *splits = 1;
@@ -459,27 +460,68 @@ int variant_for_layout(int v, const GemmArgs& g) {
   return !g.a_kc && g.b_kc ? 3 : v;
 }
 
+// Tile variant and K splits for one launch, by estimated time over the direct-to-LDS tiles.  The figures are measured, in
+// microseconds per k-tile of 64 of one tile: `busy` where as many workgroups as fit (`together`) share each compute unit,
+// `lone` where one is alone on its unit, with few and with all units at work; `rest` is what a tile takes beside its main
+// loop.  Large mini-batches keep the 256 x 256 tile, which has the best rate once it fills the chip (32768 x 4096 x 1024:
+// 242 us against 308 on 256 x 128, 322 on 128 x 128, 460 on 64 x 64); below that the smaller tiles win as soon as it
+// leaves units idle (4096 x 1024 x 4096: 80 us on 64 of its tiles, 50 to 56 on 256 of 128 x 128; 64 x 1024 x 4096: 71
+// against 20 us on 64 x 64).  K splits go through the workspace and cost a second launch and the traffic of their
+// partial sums.
+struct TileCost { int v; double busy, lone_few, lone_all, rest; int together; };
+constexpr TileCost kCostKC[] = {{5, 0.225, 0.30, 0.47, 1.5, 4}, {7, 0.60, 0.60, 0.70, 3.0, 2}, {8, 0.97, 0.80, 0.97, 4.5, 1}, {6, 1.58, 1.05, 1.58, 5.8, 1}};
+// both operands K-strided (dW)
+constexpr TileCost kCostKS[] = {{7, 0.66, 0.92, 1.12, 6.0, 2}, {8, 1.42, 1.14, 1.42, 7.0, 1}, {6, 2.20, 1.70, 2.20, 10.0, 1}};
+
+void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant, int* splits) {
+  if (g.a_kc != g.b_kc || g.nbatch != 1 || g.m_dev || g.k_dev) return pick_tile(g, out_f32, variant, splits);
+  const bool colsum = (g.epi & EPI_COLSUM) != 0, accum = out_f32 && g.epi == EPI_ACCUM;
+  const bool can_split = split_epilogue_ok(g);
+  const TileCost* cost = g.a_kc ? kCostKC : kCostKS;
+  const int ncost = g.a_kc ? 4 : 3;
+  const int nk = std::max(1, (g.K + 63) / 64);
+  double best = 1e300;
+  for (int i = 0; i < ncost; ++i) {
+    const TileCost& t = cost[i];
+    if (colsum && t.v == 5) continue;   // (partial sums come per 64 rows or more)
+    const long long tiles = (long long)((g.M + kTiles[t.v].bm - 1) / kTiles[t.v].bm) * ((g.N + kTiles[t.v].bn - 1) / kTiles[t.v].bn);
+    for (int s = 1; s <= (can_split ? std::min(64, std::max(1, nk / 2)) : 1); ++s) {
+      if (s > 1 && ((size_t)s * g.M * g.N > ws_elems || tiles * s > 512 * t.together)) break;
+      const int kt = (nk + s - 1) / s;
+      if (s > 1 && (nk + kt - 1) / kt != s) continue;   // an empty split
+      const double wgs = (double)tiles * s, per_cu = std::ceil(wgs / 256.0), rounds = std::ceil(per_cu / t.together);
+      const double lone = t.lone_few + (t.lone_all - t.lone_few) * std::min(1.0, wgs / 256.0);
+      double us = kt * std::max(rounds * lone, per_cu > 1 ? per_cu * t.busy : 0.0) + rounds * t.rest;
+      if (s > 1) us += (accum ? 4.0 : 6.0) + (double)s * g.M * g.N * 8.0 / 4.0e6;
+      if (us < best) { best = us; *variant = t.v; *splits = s; }
+    }
+  }
+}
+
 // whether gemm() will run this launch on the direct-to-LDS kernel, the one that honours EPI_COLSUM; otherwise the
 // caller runs the column-sum kernel itself
 // *rows: rows of the partial-sum matrix the kernel will fill (one per wave-tile row of C)
 bool colsum_in_gemm_ok(int dtype, bool out_f32, const GemmArgs& g, int* rows = nullptr) {
   if (!is16(dtype) || out_f32 || !mfma_ok(g) || g.nbatch != 1 || g.m_dev || g.k_dev) return false;
   int v, splits;
-  pick_tile(g, out_f32, &v, &splits);
+  GemmArgs gc = g;
+  gc.epi |= EPI_COLSUM;
+  choose_tile(gc, out_f32, 0, &v, &splits);
   if (!(kTiles[v].direct && (g.a_kc || !g.b_kc) && splits == 1)) return false;
   if (rows) *rows = (g.M + kTiles[v].wm - 1) / kTiles[v].wm;
   return gemm_vec_ok(g, g.epi | EPI_COLSUM, g.C);
 }
 
-// An accumulating fp32 GEMM split over K whose splits store their partial tiles in `ws` (fp32, room for ws_elems
-// elements; `splits` dense [M, N] slices, every element of every slice written) and are then added into C by one
-// kernel.  Returns false, with nothing launched, where the shape, the tile variant or the room do not allow it.
+// A GEMM split over K whose splits store their partial tiles in `ws` (fp32, room for ws_elems elements; `splits` dense
+// [M, N] slices, every element of every slice written) and are then added up by one kernel, which adds them into C
+// (accumulating fp32 GEMMs) or applies the launch's epilogue.  Returns false, with nothing launched, where the shape, the tile variant or the room do not allow it.
 enum { SPLIT_NOT_APPLICABLE = 0, SPLIT_LAUNCHED = 1, SPLIT_NO_ROOM = 2 };
 int launch_split_through_workspace(int v, const GemmArgs& g, hipStream_t s, int splits, bool out_f32, bool fp16_in, float* ws,
                                    size_t ws_elems) {
   const long long slice = (long long)g.M * g.N;
-  if (!(splits > 1 && out_f32 && g.epi == EPI_ACCUM && kTiles[v].direct && g.nbatch == 1 && g.N % 8 == 0 && g.ldc % 4 == 0 &&
-        ((uintptr_t)g.C & 15) == 0 && ws && !g.m_dev && !g.k_dev))
+  const bool accum = out_f32 && g.epi == EPI_ACCUM;
+  if (!(splits > 1 && kTiles[v].direct && g.nbatch == 1 && ws && !g.m_dev && !g.k_dev &&
+        (accum ? g.N % 8 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0 : split_epilogue_ok(g))))
     return SPLIT_NOT_APPLICABLE;
   const int nk = (g.K + kTiles[v].bk - 1) / kTiles[v].bk, per = (nk + splits - 1) / splits;
   splits = (nk + per - 1) / per;   // no empty split: every slice of the workspace gets written
@@ -488,8 +530,10 @@ int launch_split_through_workspace(int v, const GemmArgs& g, hipStream_t s, int 
   GemmArgs p = g;
   p.C = ws; p.ldc = g.N; p.split_stride = slice; p.epi = 0;
   const unsigned blocks = (unsigned)std::min<long long>((slice / 4 + 255) / 256, 4096);
-  launch_mfma_variant(v, p, s, splits, out_f32, fp16_in);
-  hipLaunchKernelGGL(split_sum_kernel, dim3(blocks), dim3(256), 0, s, ws, splits, (long long)g.M, g.N, (float*)g.C, g.ldc);
+  launch_mfma_variant(v, p, s, splits, true, fp16_in);
+  if (accum) hipLaunchKernelGGL(split_sum_kernel, dim3(blocks), dim3(256), 0, s, ws, splits, (long long)g.M, g.N, (float*)g.C, g.ldc);
+  else if (fp16_in) out_f32 ? launch_split_epilogue<fp16, float>(g, ws, splits, s) : launch_split_epilogue<fp16, fp16>(g, ws, splits, s);
+  else out_f32 ? launch_split_epilogue<bf16, float>(g, ws, splits, s) : launch_split_epilogue<bf16, bf16>(g, ws, splits, s);
   return SPLIT_LAUNCHED;
 }
 
@@ -521,8 +565,12 @@ int gemm(l2l_ctx* c, int dtype, bool out_f32, const GemmArgs& g, int impl = 0, i
   }
   return timed(c, cls, flops, bytes, [&] {
     if (use_mfma) {
+      // with a workspace for partial sums the tile and the splits are chosen by estimated time; a forced tile, forced
+      // splits and splits that add with atomics keep the rule by size
+      const bool by_time = impl < 100 && c->force_splits == 0 && !c->split_atomics && c->split_ws;
       int v, splits;
-      pick_tile(g, out_f32, &v, &splits);
+      if (by_time || (g.epi & EPI_COLSUM)) choose_tile(g, out_f32, c->split_ws_elems, &v, &splits);
+      else pick_tile(g, out_f32, &v, &splits);
       if (impl >= 100) v = impl - 100;
       v = variant_for_layout(v, g);
       if (c->force_splits > 0 && out_f32 && g.epi == EPI_ACCUM) splits = c->force_splits;
@@ -1223,34 +1271,24 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
   for (auto& b : bufs) L2L_TRY(dev_alloc(c, b.p, b.n * es));
   if (is16(cfg->dtype) && !c->no_weight_transpose)
     for (int i = 0; i < 2; ++i) L2L_TRY(dev_alloc(c, &c->wt[i], c->lay.total * es));
-  if (is16(cfg->dtype)) {   // workspace of the K-split dW GEMMs: the largest of the layer's four, by the split rule in use
-    size_t need = 0;
-    const int h = cfg->hidden, f = cfg->ffn;
-    const int shapes[4][2] = {{h, 3 * h}, {h, h}, {h, f}, {f, h}};
-    for (const auto& s : shapes) {
-      GemmArgs w = gemm_args(s[0], s[1], (int)Mg, nullptr, s[0], 0, nullptr, s[1], 0, nullptr, s[1]);
-      w.epi = EPI_ACCUM;
-      int v, splits;
-      pick_tile(w, true, &v, &splits);
-      if (splits > 1) need = std::max(need, (size_t)splits * s[0] * s[1]);
-    }
-    if (const char* e = getenv("L2L_SPLIT_WS_MB")) need = (size_t)atoll(e) << 18;   // tuning: room for other split factors
-    if (need > 0 && need * 4 <= (size_t)256 << 20) {
-      c->split_ws_elems = need;
-      L2L_TRY(dev_alloc(c, (void**)&c->split_ws, need * 4));
-    }
-  }
-  if (!is16(cfg->dtype)) {   // fp32: the largest room that the K splits of the layer's GEMMs ask for, within 32 MB
-    constexpr size_t kMost = (size_t)8 << 20;
+  {   // workspace of the K-split GEMMs: the largest room that the layer's shapes ask for, within 64 MB (fp32: 32 MB)
+    const bool f32 = !is16(cfg->dtype);
+    const size_t most = (size_t)(f32 ? 8 : 16) << 20;
     size_t need = 0;
     const int h = cfg->hidden, f = cfg->ffn, m = (int)Mg;
     const int shapes[][3] = {{m, 3 * h, h}, {m, h, h}, {m, f, h}, {m, h, f}, {m, h, 3 * h}, {h, 3 * h, m}, {h, h, m}, {h, f, m}, {f, h, m}};
-    for (const auto& s : shapes) {
-      GemmArgs g = gemm_args(s[0], s[1], s[2], nullptr, s[2], 1, nullptr, s[2], 1, nullptr, s[1]);
-      const int splits = pick_f32_splits(g, kMost);
+    for (int i = 0; i < 9; ++i) {
+      const auto& s = shapes[i];
+      const int kc = i < 5;   // the last four are the dW shapes
+      GemmArgs g = gemm_args(s[0], s[1], s[2], nullptr, kc ? s[2] : s[0], kc, nullptr, kc ? s[2] : s[1], kc, nullptr, s[1]);
+      if (!kc) g.epi = EPI_ACCUM;
+      int v = 0, splits = 1;
+      if (f32) splits = pick_f32_splits(g, most);
+      else choose_tile(g, !kc, most, &v, &splits);
       if (splits > 1) need = std::max(need, (size_t)splits * s[0] * s[1]);
     }
-    if (const char* e = getenv("L2L_SPLIT_WS_MB")) need = (size_t)atoll(e) << 18;
+    if (const char* e = getenv("L2L_SPLIT_WS_MB")) need = (size_t)atoll(e) << 18;   // tuning: room for other split factors
+    if (need == 0 && !f32) need = 64;   // (the 16-bit launches choose their tile by time where a workspace exists)
     if (need > 0) {
       c->split_ws_elems = need;
       L2L_TRY(dev_alloc(c, (void**)&c->split_ws, need * 4));

@@ -260,6 +260,24 @@ def test_gemm_every_compiled_epilogue_elementwise(ctx, dtype, epi):
     _report(f"gemm_ex[{dtype}-epi{epi}]", {"C": errs[0], "max:C": errs[1]})
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (64, 1024, 4096), (72, 264, 2056), (328, 520, 1032), (1000, 136, 4104)])
+def test_gemm_small_launches_elementwise(monkeypatch, M, N, K, dtype):
+    # launches that leave most of the chip idle on large tiles: 64 x 64 and 128 x 128 tiles, K splits through the workspace
+    # with every epilogue of the layer, tails in M, N and K
+    monkeypatch.setenv("L2L_SPLIT_WS_MB", "64")
+    c = P.Context(P.make_config(64, 2, 128, 16, 2, 2, "bf16", 1e-5, 0))
+    try:
+        for epi in (0, 1, 9, 3, 67, 128, 8):
+            _gemm_ex_case(c, dtype, M, N, K, seed=M + epi, **EPILOGUES[epi])
+        _gemm_ex_case(c, dtype, M, N, K, out_f32=True, bias=True, seed=M)
+        _gemm_ex_case(c, dtype, M, N, K, out_f32=True, accumulate=True, seed=M)
+        if M % 8 == 0:
+            _gemm_ex_case(c, dtype, M, N, K, a_kc=0, b_kc=0, out_f32=True, accumulate=True, seed=M)
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("K", [136, 1032])
 @pytest.mark.parametrize("epi", [9, 67, 160])
 def test_gemm_resident_tile_walk_elementwise(ctx, K, epi):

@@ -1,7 +1,8 @@
-// Fused attention for the 16-bit paths (element type E = bf16 or fp16), head width d = 64, sequence length a
-// multiple of 32 up to 128: scores, softmax and context (forward) and all five attention gradients (backward)
+// Fused attention for the 16-bit paths (element type E = bf16 or fp16).  First the kernels for head width d = 64 and a
+// sequence length that is a multiple of 32 up to 128: scores, softmax and context (forward) and all five attention gradients (backward)
 // of one (sequence, head) pair in one workgroup, without the S x S matrices ever leaving the chip.  Longer
-// sequences (multiples of 32) go through the chunked kernels at the end of this file.
+// sequences (multiples of 32) go through the chunked kernels further down, other lengths and head widths up to 128
+// through the padding ones at the end of this file.
 //
 // Everything is computed "transposed": the MFMA tiles are S^T = K Q^T (keys along the accumulator's
 // register axis, queries along its lane axis), so that a softmax row lives in the registers of one
@@ -689,6 +690,313 @@ void attn_bwd_dkv_long_kernel(const E* qkv, const E* dout, const float* lse, con
   E* out = dqkv + ((long long)b * S + kc * CH + wave * 32) * ld + h * 64;
   store_T(dv, out + 2 * H, ld, lane, 1.0f);
   store_T(dk, out + H, ld, lane, alpha);
+}
+
+// ---- any head width up to 128, any sequence length that is a multiple of 8 -------------------------------------
+// The same three kernels as for long sequences, with the head width padded to DP = 32, 64, 96 or 128: columns d .. DP - 1
+// of every image and fragment are zeros (16-byte chunks past d are sent out of the descriptor's range), keys past S get
+// no weight, queries past S are computed on zeros and not stored.  A workgroup owns 128 queries (or keys) and walks the
+// other index in chunks of 64 rows, which keeps two images of the widest head within 32 KB and several workgroups on a
+// compute unit: nothing is prefetched, the other workgroups run under one's loads.
+// Bound by the latency of the chain load -> products -> softmax -> products at these sizes.  Measured at 35 sequences of
+// 200 tokens with 12 heads of 96, against the batched GEMM launches around softmax kernels they replace, which wrote S x S
+// matrices to memory and read them back: forward 121 -> 35 us, backward 183 -> 94 us.
+constexpr int CHA = 64;   // rows per chunk
+
+template <int DP>
+struct Any {
+  static constexpr int NC = DP / 8, PITCH = DP * 2, IMG = CHA * PITCH;   // 16-byte chunks per row, bytes per row and image
+  // slot of chunk c in row r, and back: 16 rows' reads of one chunk spread over the banks
+  static __device__ __forceinline__ int slot(int r, int c) {
+    if constexpr (NC == 16) return c ^ (r & 15);
+    else if constexpr (NC == 8) return c ^ ((r >> 1) & 7);
+    else if constexpr (NC == 4) return c ^ ((r >> 2) & 3);
+    else { const int s = c + ((r >> 2) & 3); return s < NC ? s : s - NC; }   // (12 is no power of two: a rotation)
+  }
+  static __device__ __forceinline__ int chunk(int r, int s) {
+    if constexpr (NC == 12) { const int c = s - ((r >> 2) & 3); return c >= 0 ? c : c + NC; }
+    else return slot(r, s);
+  }
+  // `rows` (<= CHA) rows of d columns into the image; everything else of it becomes zero
+  static __device__ __forceinline__ void load(const void* base, uint32_t ld, int rows, int d, char* dst, int wave, int lane) {
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, (uint32_t)(((long long)(rows - 1) * ld + d) * 2));
+#pragma unroll
+    for (int i = 0; i < IMG / 4096; ++i) {
+      const int blk = i * 4 + wave, idx = blk * 64 + lane, row = idx / NC, c = chunk(row, idx % NC);
+      const uint32_t off = c * 8 < d && row < rows ? ((uint32_t)row * ld + (uint32_t)c * 8) * 2u : BUF_OOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + blk * 1024), 16, (int)off, 0, 0, 0);
+    }
+  }
+  static __device__ __forceinline__ bf16x8 rows_frag(const char* img, int row, int step, int lane) {
+    return *(const bf16x8*)(img + row * PITCH + slot(row, step * 2 + (lane >> 5)) * 16);
+  }
+  static __device__ __forceinline__ s16x4 tr(const char* img, int row0, int col0, int lane) {
+    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
+    const int i16 = lane & 15, row = row0 + (i16 >> 2), col = col0 + 16 * ((lane >> 4) & 1) + (i16 & 3) * 4;
+    const char* p = img + row * PITCH + slot(row, col >> 3) * 16 + (col & 7) * 2;
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(__attribute__((address_space(3))) char*)p);
+  }
+  // as frag_keys_T: rows rb*32 + 16 s + 4 (lane / 32) + {0..3} and those + 8, columns 32 t ..
+  static __device__ __forceinline__ bf16x8 rows_T(const char* img, int rb, int s, int t, int lane) {
+    const int base = rb * 32 + 16 * s + 4 * (lane >> 5);
+    const s16x4 lo = tr(img, base, t * 32, lane), hi = tr(img, base + 8, t * 32, lane);
+    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  }
+  // B-operand fragments of one row of memory (or zeros), columns 16 st + 8 (lane / 32) ..
+  template <typename E>
+  static __device__ __forceinline__ void row_frags(const E* row, bool live, int d, int lane, bf16x8 (&f)[DP / 16]) {
+#pragma unroll
+    for (int st = 0; st < DP / 16; ++st) {
+      const int c = st * 16 + (lane >> 5) * 8;
+      f[st] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+      if (live && c < d) f[st] = *(const bf16x8*)(row + c);
+    }
+  }
+  // transposed accumulators (lane = row of the output) to row[0 .. d)
+  template <typename E>
+  static __device__ __forceinline__ void store(const f32x16 (&acc)[DP / 32], E* row, int d, int lane, float scale) {
+#pragma unroll
+    for (int t = 0; t < DP / 32; ++t)
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk) {
+        const int c = t * 32 + blk * 8 + 4 * (lane >> 5);
+        typename Vec<E>::x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = from_f32<E>(acc[t][blk * 4 + i] * scale);
+        if (c < d) *(typename Vec<E>::x4*)(row + c) = v;
+      }
+  }
+};
+
+__device__ __forceinline__ f32x16 zero16() { return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; }
+
+template <typename E, int DP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void attn_fwd_any_kernel(const E* qkv, E* out, float* lse, int S, int H, int A, int d, float alpha) {
+  using I = Any<DP>;
+  __shared__ __attribute__((aligned(1024))) char lds[2 * I::IMG];
+  char* Ks = lds;
+  char* Vs = lds + I::IMG;
+  const int nq = (S + 127) / 128;
+  const int qb = blockIdx.x % nq, bh = blockIdx.x / nq, b = bh / A, h = bh % A;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long ld = 3LL * H;
+  const E* base = qkv + (long long)b * S * ld + h * d;
+  const int q = qb * 128 + wave * 32 + (lane & 31);
+  const bool active = qb * 128 + wave * 32 < S;   // (per wave)
+  bf16x8 qf[DP / 16];
+  I::template row_frags<E>(base + (long long)q * ld, q < S, d, lane, qf);
+  float m = -INFINITY, sum = 0.f;
+  f32x16 o[DP / 32];
+#pragma unroll
+  for (int t = 0; t < DP / 32; ++t) o[t] = zero16();
+  for (int k0 = 0; k0 < S; k0 += CHA) {
+    const int rows = min(CHA, S - k0);   // this chunk's keys
+    if (k0) __syncthreads();             // every wave has left the previous chunk
+    I::load(base + H + (long long)k0 * ld, (uint32_t)ld, rows, d, Ks, wave, lane);
+    I::load(base + 2 * H + (long long)k0 * ld, (uint32_t)ld, rows, d, Vs, wave, lane);
+    wait_vm0();
+    __syncthreads();
+    if (!active) continue;
+    f32x16 p[2];
+    float cm = m;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+      if (kb * 32 < rows) {
+        f32x16 a = zero16();
+#pragma unroll
+        for (int st = 0; st < DP / 16; ++st) a = mfma_32x32x16<E>(I::rows_frag(Ks, kb * 32 + (lane & 31), st, lane), qf[st], a);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) a[r] *= alpha;
+        if (kb * 32 + 32 > rows) {   // keys past S: no weight
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (kb * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) >= rows) a[r] = -INFINITY;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) cm = fmaxf(cm, a[r]);
+        p[kb] = a;
+      }
+    cm = xor32_max(cm);
+    const float rescale = __expf(m - cm);   // 0 on the first chunk
+    m = cm;
+    float cs = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+      if (kb * 32 < rows) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { p[kb][r] = __expf(p[kb][r] - m); cs += p[kb][r]; }
+      }
+    sum = sum * rescale + xor32_sum(cs);
+#pragma unroll
+    for (int t = 0; t < DP / 32; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[t][r] *= rescale;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+      if (kb * 32 < rows) {
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const bf16x8 pf = pack8<E>(p[kb], 8 * s2);
+#pragma unroll
+          for (int t = 0; t < DP / 32; ++t) o[t] = mfma_32x32x16<E>(I::rows_T(Vs, kb, s2, t, lane), pf, o[t]);
+        }
+      }
+  }
+  if (q >= S) return;
+  I::template store<E>(o, out + ((long long)b * S + q) * H + h * d, d, lane, 1.0f / sum);
+  if (lse && lane < 32) lse[(long long)bh * S + q] = m + __logf(sum);
+}
+
+// as attn_bwd_dq_long_kernel
+template <typename E, int DP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void attn_bwd_dq_any_kernel(const E* qkv, const E* dout, const E* ctx, const float* lse, float* dsum, E* dqkv, int S, int H, int A,
+                            int d, float alpha) {
+  using I = Any<DP>;
+  __shared__ __attribute__((aligned(1024))) char lds[2 * I::IMG];
+  char* Ks = lds;
+  char* Vs = lds + I::IMG;
+  const int nq = (S + 127) / 128;
+  const int qb = blockIdx.x % nq, bh = blockIdx.x / nq, b = bh / A, h = bh % A;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long ld = 3LL * H;
+  const E* base = qkv + (long long)b * S * ld + h * d;
+  const int q = qb * 128 + wave * 32 + (lane & 31);
+  const bool active = qb * 128 + wave * 32 < S;   // (per wave)
+  bf16x8 qf[DP / 16], of[DP / 16];
+  const long long orow = ((long long)b * S + q) * H + h * d;
+  I::template row_frags<E>(base + (long long)q * ld, q < S, d, lane, qf);
+  I::template row_frags<E>(dout + orow, q < S, d, lane, of);
+  float D = 0.f, L = 0.f;
+  if (q < S) {
+#pragma unroll
+    for (int st = 0; st < DP / 16; ++st) {
+      const int c = st * 16 + (lane >> 5) * 8;
+      if (c < d) {
+        const typename Vec<E>::x8 gv = __builtin_bit_cast(typename Vec<E>::x8, of[st]);
+        const typename Vec<E>::x8 cv = *(const typename Vec<E>::x8*)(ctx + orow + c);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) D += to_f32(gv[i]) * to_f32(cv[i]);
+      }
+    }
+    L = lse[(long long)bh * S + q];
+  }
+  D = xor32_sum(D);
+  if (q < S && lane < 32) dsum[(long long)bh * S + q] = D;
+  f32x16 dq[DP / 32];
+#pragma unroll
+  for (int t = 0; t < DP / 32; ++t) dq[t] = zero16();
+  for (int k0 = 0; k0 < S; k0 += CHA) {
+    const int rows = min(CHA, S - k0);
+    if (k0) __syncthreads();
+    I::load(base + H + (long long)k0 * ld, (uint32_t)ld, rows, d, Ks, wave, lane);
+    I::load(base + 2 * H + (long long)k0 * ld, (uint32_t)ld, rows, d, Vs, wave, lane);
+    wait_vm0();
+    __syncthreads();
+    if (!active) continue;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+      if (kb * 32 < rows) {
+        f32x16 a = zero16(), g = zero16();
+#pragma unroll
+        for (int st = 0; st < DP / 16; ++st) {
+          a = mfma_32x32x16<E>(I::rows_frag(Ks, kb * 32 + (lane & 31), st, lane), qf[st], a);
+          g = mfma_32x32x16<E>(I::rows_frag(Vs, kb * 32 + (lane & 31), st, lane), of[st], g);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) g[r] = __expf(a[r] * alpha - L) * (g[r] - D);   // dP -> dS
+        if (kb * 32 + 32 > rows) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (kb * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) >= rows) g[r] = 0.f;
+        }
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const bf16x8 df = pack8<E>(g, 8 * s2);
+#pragma unroll
+          for (int t = 0; t < DP / 32; ++t) dq[t] = mfma_32x32x16<E>(I::rows_T(Ks, kb, s2, t, lane), df, dq[t]);
+        }
+      }
+  }
+  if (q >= S) return;
+  I::template store<E>(dq, dqkv + ((long long)b * S + q) * ld + h * d, d, lane, alpha);
+}
+
+// as attn_bwd_dkv_long_kernel (the widest head needs more than half of a SIMD's registers per wave)
+template <typename E, int DP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP > 96 ? 1 : 2)))
+void attn_bwd_dkv_any_kernel(const E* qkv, const E* dout, const float* lse, const float* dsum, E* dqkv, int S, int H, int A, int d,
+                             float alpha) {
+  using I = Any<DP>;
+  __shared__ __attribute__((aligned(1024))) char lds[2 * I::IMG];
+  __shared__ __attribute__((aligned(16))) float Ls[CHA], Dsm[CHA];
+  char* Qs = lds;
+  char* Os = lds + I::IMG;
+  const int nkv = (S + 127) / 128;
+  const int kc = blockIdx.x % nkv, bh = blockIdx.x / nkv, b = bh / A, h = bh % A;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const long long ld = 3LL * H;
+  const E* base = qkv + (long long)b * S * ld + h * d;
+  const E* dob = dout + (long long)b * S * H + h * d;
+  const int key = kc * 128 + wave * 32 + (lane & 31);
+  const bool active = kc * 128 + wave * 32 < S;   // (per wave)
+  bf16x8 kf[DP / 16], vf[DP / 16];
+  I::template row_frags<E>(base + H + (long long)key * ld, key < S, d, lane, kf);
+  I::template row_frags<E>(base + 2 * H + (long long)key * ld, key < S, d, lane, vf);
+  f32x16 dv[DP / 32], dk[DP / 32];
+#pragma unroll
+  for (int t = 0; t < DP / 32; ++t) { dv[t] = zero16(); dk[t] = zero16(); }
+  for (int q0 = 0; q0 < S; q0 += CHA) {
+    const int rows = min(CHA, S - q0);   // this chunk's queries; those past S are rows of zeros with lse = dsum = 0: they add nothing
+    if (q0) __syncthreads();
+    I::load(base + (long long)q0 * ld, (uint32_t)ld, rows, d, Qs, wave, lane);
+    I::load(dob + (long long)q0 * H, (uint32_t)H, rows, d, Os, wave, lane);
+    if (tid < CHA) {
+      const long long srow = (long long)bh * S + q0 + tid;
+      Ls[tid] = tid < rows ? lse[srow] : 0.f;
+      Dsm[tid] = tid < rows ? dsum[srow] : 0.f;
+    }
+    wait_vm0();
+    __syncthreads();
+    if (!active) continue;
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      if (qb * 32 >= rows) break;
+      f32x16 a = zero16(), g = zero16();
+#pragma unroll
+      for (int st = 0; st < DP / 16; ++st) {
+        a = mfma_32x32x16<E>(I::rows_frag(Qs, qb * 32 + (lane & 31), st, lane), kf[st], a);
+        g = mfma_32x32x16<E>(I::rows_frag(Os, qb * 32 + (lane & 31), st, lane), vf[st], g);
+      }
+      // register r of this lane belongs to query 32 qb + 8 (r / 4) + 4 (lane / 32) + r % 4
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk) {
+        const f32x4 L4 = *(const f32x4*)(Ls + qb * 32 + 8 * blk + 4 * (lane >> 5));
+        const f32x4 D4 = *(const f32x4*)(Dsm + qb * 32 + 8 * blk + 4 * (lane >> 5));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float p = __expf(a[4 * blk + i] * alpha - L4[i]);
+          a[4 * blk + i] = p;
+          g[4 * blk + i] = p * (g[4 * blk + i] - D4[i]);
+        }
+      }
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const bf16x8 pf = pack8<E>(a, 8 * s2), gf = pack8<E>(g, 8 * s2);
+#pragma unroll
+        for (int t = 0; t < DP / 32; ++t) {
+          dv[t] = mfma_32x32x16<E>(I::rows_T(Os, qb, s2, t, lane), pf, dv[t]);
+          dk[t] = mfma_32x32x16<E>(I::rows_T(Qs, qb, s2, t, lane), gf, dk[t]);
+        }
+      }
+    }
+  }
+  if (key >= S) return;
+  E* row = dqkv + ((long long)b * S + key) * ld + h * d;
+  I::template store<E>(dv, row + 2 * H, d, lane, 1.0f);
+  I::template store<E>(dk, row + H, d, lane, alpha);
 }
 
 }  // namespace attn

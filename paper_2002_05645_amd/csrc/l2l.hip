@@ -737,6 +737,20 @@ bool fused_attention_long_ok(const l2l_ctx* c) {
   return is16(f.dtype) && f.hidden / f.heads == 64 && f.seq % 32 == 0 && f.seq > attn::SMAX && !c->no_fused_attention;
 }
 
+// ... and every other sequence length and head widths up to 128 the kernels that pad both
+bool fused_attention_any_ok(const l2l_ctx* c) {
+  const l2l_config& f = c->cfg;
+  return is16(f.dtype) && f.hidden / f.heads <= 128 && !c->no_fused_attention && !fused_attention_ok(c) && !fused_attention_long_ok(c);
+}
+// f(integral_constant<int, DP>) for the padded head width DP = 32, 64, 96 or 128
+template <typename F>
+void with_padded_head(int d, F&& f) {
+  if (d <= 32) f(std::integral_constant<int, 32>{});
+  else if (d <= 64) f(std::integral_constant<int, 64>{});
+  else if (d <= 96) f(std::integral_constant<int, 96>{});
+  else f(std::integral_constant<int, 128>{});
+}
+
 int fill_zero(l2l_ctx* c, void* p, size_t bytes) {
   const long long n = (long long)(bytes / 4);
   if (n <= 0) return L2L_OK;
@@ -813,6 +827,15 @@ int layer_forward_group(l2l_ctx* c, int slot, const void* x, void* y, int ng, bo
                            keep ? c->lse : nullptr, S, H, A, 1.0f / sqrtf((float)d));
       };
       if (S % attn::CH) go(attn::attn_fwd_long_kernel<E, true>); else go(attn::attn_fwd_long_kernel<E, false>);
+    }));
+  } else if (fused_attention_any_ok(c)) {
+    const double fl = 4.0 * S * S * d * nseq * A;
+    L2L_TRY(timed(c, L2L_PROF_ATTN, fl, (3.0 + 1.0) * M * H * sizeof(T), [&] {
+      using E = attn_elem<T>;
+      with_padded_head(d, [&](auto dp) {
+        hipLaunchKernelGGL((attn::attn_fwd_any_kernel<E, decltype(dp)::value>), dim3(nseq * A * ((S + 127) / 128)), dim3(256), 0, c->cs,
+                           (const E*)qkv, (E*)c->c, keep ? c->lse : nullptr, S, H, A, d, 1.0f / sqrtf((float)d));
+      });
     }));
   } else
   {
@@ -976,6 +999,21 @@ int layer_backward_group(l2l_ctx* c, const void* params, const void* x, void* dy
                            alpha);
       };
       if (S % attn::CH) go(attn::attn_bwd_dkv_long_kernel<E, true>); else go(attn::attn_bwd_dkv_long_kernel<E, false>);
+    }));
+  } else if (fused_attention_any_ok(c)) {
+    using E = attn_elem<T>;
+    const dim3 grid(nseq * A * ((S + 127) / 128));
+    L2L_TRY(timed(c, L2L_PROF_ATTN, 4.0 * S * S * d * nseq * A, (3.0 + 1.0 + 1.0 + 1.0) * M * H * sizeof(T), [&] {
+      with_padded_head(d, [&](auto dp) {
+        hipLaunchKernelGGL((attn::attn_bwd_dq_any_kernel<E, decltype(dp)::value>), grid, dim3(256), 0, c->cs, (const E*)qkv,
+                           (const E*)c->dc, (const E*)c->c, c->lse, c->dsum, (E*)dqkv, S, H, A, d, alpha);
+      });
+    }));
+    L2L_TRY(timed(c, L2L_PROF_ATTN, 6.0 * S * S * d * nseq * A, (3.0 + 1.0 + 2.0) * M * H * sizeof(T), [&] {
+      with_padded_head(d, [&](auto dp) {
+        hipLaunchKernelGGL((attn::attn_bwd_dkv_any_kernel<E, decltype(dp)::value>), grid, dim3(256), 0, c->cs, (const E*)qkv,
+                           (const E*)c->dc, c->lse, c->dsum, (E*)dqkv, S, H, A, d, alpha);
+      });
     }));
   } else
   {
@@ -1252,7 +1290,7 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
   const size_t es = esize(cfg->dtype);
   const long long H = cfg->hidden, F = cfg->ffn, S = cfg->seq, A = cfg->heads, Mg = c->Mg;
   // the attention matrices P and dP exist in memory only on the batched-GEMM path
-  const bool fused = fused_attention_ok(c) || fused_attention_long_ok(c);
+  const bool chunked = fused_attention_long_ok(c) || fused_attention_any_ok(c), fused = fused_attention_ok(c) || chunked;
   const long long pe = fused ? 0 : (long long)g * cfg->ubatch * A * S * S;
   for (int i = 0; i < 2; ++i) {
     L2L_TRY(dev_alloc(c, &c->slot[i], c->lay.total * es));
@@ -1302,7 +1340,7 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
   HIP_TRY(c, hipMemset(c->bad_ids, 0, 4));
   float** stats[] = {&c->mean1, &c->rstd1, &c->mean2, &c->rstd2};
   for (auto s : stats) L2L_TRY(dev_alloc(c, (void**)s, Mg * 4));
-  if (fused_attention_long_ok(c)) {   // per (sequence, head, query): log-sum-exp of the scores, rowsum(dO O)
+  if (chunked) {   // per (sequence, head, query): log-sum-exp of the scores, rowsum(dO O)
     L2L_TRY(dev_alloc(c, (void**)&c->lse, Mg * A * 4));
     L2L_TRY(dev_alloc(c, (void**)&c->dsum, Mg * A * 4));
   }

@@ -553,6 +553,15 @@ def test_layer_chunked_attention_long_sequences(seq, dtype):
     _assert_errs(_layer_case(w, group=2, **kw), TOL[dtype])     # ragged last group
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("d,seq", [(8, 8), (32, 64), (40, 136), (64, 40), (64, 200), (72, 24), (80, 264), (96, 200), (104, 72), (128, 128), (128, 328)])
+def test_layer_attention_any_head_width_and_length(d, seq, dtype):
+    # head widths padded to 32, 64, 96 and 128 columns, sequences that end inside a block of 32, a chunk of 64 and a
+    # workgroup's 128 rows (fp16: upstream gradients as a scaled loss leaves them, see the case above)
+    w = S.Workload("any", 1, 2 * d, 2, 8 * d, seq, 50, 3, 2, dtype, 1.0, 500 + seq + d)
+    _assert_errs(_layer_case(w, dy_scale=256.0 if dtype == "fp16" else 1.0), TOL[dtype])
+
+
 @pytest.mark.parametrize("seq", [160, 512])
 def test_layer_chunked_attention_fp16_unscaled_gradient(seq):
     # The same fp16 cases WITHOUT the factor on dY: upstream gradients of size 1e-3 times attention weights of size

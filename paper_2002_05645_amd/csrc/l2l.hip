@@ -1111,8 +1111,17 @@ int head_loss_t(l2l_ctx* c, const void* x_last, const int32_t* labels, void* dy_
     g.epi = EPI_BIAS; g.bias = E + eo[E_BV]; g.m_dev = cnt;
     L2L_TRY(gemm(c, dt, true, g, 0, L2L_PROF_OTHER));
     L2L_TRY(timed(c, L2L_PROF_OTHER, 0, 0, [&] {
-      hipLaunchKernelGGL(ce_kernel<T>, dim3(rows), dim3(256), 0, c->cs, c->logits, Vp, labels, idx, cnt, c->lab_total, (T*)c->dz,
-                         loss_out, V, (int)Vp, c->loss_scale, c->bad_ids);
+      // the row in registers as far as 512 threads can hold it (vocabularies up to 32768), else the loop over memory
+      const auto go = [&](auto kern, unsigned blocks, unsigned threads) {
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(threads), 0, c->cs, c->logits, Vp, labels, idx, cnt, c->lab_total, (T*)c->dz,
+                           loss_out, V, (int)Vp, c->loss_scale, c->bad_ids);
+      };
+      const unsigned blocks = (unsigned)std::min(rows, 2048);
+      if (Vp <= 4 * CE_NT) go(ce_row_kernel<T, 1>, blocks, CE_NT);
+      else if (Vp <= 16 * CE_NT) go(ce_row_kernel<T, 4>, blocks, CE_NT);
+      else if (Vp <= 32 * CE_NT) go(ce_row_kernel<T, 8>, blocks, CE_NT);
+      else if (Vp <= 64 * CE_NT) go(ce_row_kernel<T, 16>, blocks, CE_NT);
+      else go(ce_kernel<T>, (unsigned)rows, 256);
     }));
     // dXl = dz E
     if constexpr (sizeof(T) == 2) {

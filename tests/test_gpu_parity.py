@@ -1087,3 +1087,61 @@ def test_call_order_errors():
         c.sync()
     finally:
         c.close()
+
+
+def _head_case(vocab, hidden, seqs, seq, dtype, label_prob, seed):
+    """loss, dL/dX, dE and dbv of the LM head against the same in 64 bits; returns their relative errors"""
+    cfg = P.make_config(hidden, 1, 64, seq, seqs, 1, dtype, 1e-12, vocab=vocab)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16, "fp16": torch.float16}[dtype]
+    layout, total = P.embed_layout(cfg), P.lib().l2l_embed_packed_elems(cfg)
+    rows = seqs * seq
+    c = P.Context(cfg)
+    block = (torch.randn(total, device="cuda", generator=gen) * 0.05).to(dt)
+    host = block.cpu().pin_memory()
+    c.embed_stage(host)
+    x = torch.randn((1, seqs, seq, hidden), device="cuda", generator=gen).to(dt)
+    lab = torch.randint(0, vocab, (1, seqs, seq), dtype=torch.int32, device="cuda", generator=gen)
+    drop = torch.rand(lab.shape, device="cuda", generator=gen) >= label_prob
+    drop.view(-1)[0] = False
+    lab = torch.where(drop, torch.full_like(lab, -1), lab)
+    dy, loss = torch.empty_like(x), torch.zeros(1, device="cuda")
+    if dtype == "fp16":
+        c.set_loss_scale(1024.0)
+    tok = torch.zeros((1, seqs, seq), dtype=torch.int32, device="cuda")
+    c.embed_fwd(tok, torch.empty_like(x))
+    c.head_loss(x, lab, dy, loss)
+    c.embed_bwd(tok, torch.zeros_like(x))
+    land = torch.zeros(total).pin_memory()
+    c.embed_grad_drain(land)
+    c.sync()
+    c.close()
+    scale = 1024.0 if dtype == "fp16" else 1.0
+    E = block[layout["E"][0]:][:vocab * hidden].view(vocab, hidden).double()
+    bv = block[layout["bv"][0]:][:vocab].double()
+    live = (lab.view(-1) >= 0).nonzero().view(-1)
+    xl, ll = x.view(rows, hidden)[live].double(), lab.view(-1)[live].long()
+    z = xl @ E.t() + bv
+    lse = torch.logsumexp(z, 1)
+    ref_loss = (lse - z.gather(1, ll[:, None])[:, 0]).mean()
+    dz = torch.softmax(z, 1)
+    dz[torch.arange(len(ll), device="cuda"), ll] -= 1.0
+    dz *= scale / len(ll)
+    dx = torch.zeros(rows, hidden, dtype=torch.float64, device="cuda")
+    dx[live] = dz @ E
+    rel = lambda a, b: float((a.double().cpu().view(-1) - b.cpu().view(-1)).norm() / b.norm())
+    return {"loss": abs(float(loss) - float(ref_loss)) / abs(float(ref_loss)), "dx": rel(dy, dx),
+            "dE": rel(land[layout["E"][0]:][:vocab * hidden], dz.t() @ xl), "dbv": rel(land[layout["bv"][0]:][:vocab], dz.sum(0))}
+
+
+# dz and dX are rounded once each to the format (2^-9 of a value for bf16, 2^-12 for fp16, at most), sums are in fp32
+HEAD_TOL = {"fp32": 1e-5, "bf16": 2 * 2.0 ** -9, "fp16": 2 * 2.0 ** -12}
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("vocab", [2, 62, 2048, 2050, 8194, 16382, 16386, 32768, 32770])
+def test_head_vocabulary_sizes(vocab, dtype):
+    # cross-entropy with the row in registers of 512 threads: 1, 4, 8 and 16 chunks of 4 columns each, their edges, and
+    # the loop over memory beyond 32768
+    errs = _head_case(vocab, 64, 3, 24, dtype, 0.7, vocab)
+    assert all(e <= HEAD_TOL[dtype] for e in errs.values()), errs

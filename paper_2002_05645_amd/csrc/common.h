@@ -206,9 +206,27 @@ struct GemmArgs {
                           // split s stores its partial result at C + s * split_stride (elements) and the caller adds them up
   int resident;           // direct-to-LDS kernel: > 0 = launch at most this many workgroups (one per compute unit) and let
                           // each walk its share of the tile order; 0 = one workgroup per tile
+  int live_splits;        // 1: K splits by live_splits(*m_dev, N, K), partial results to C (256 x 256 tiles, A K-contiguous, B K-strided)
   float* colsum;          // EPI_COLSUM: fp32 [ceil(M / WM)][N] (WM = rows of a wave's tile): row r receives the column sums
                           // of the values stored to rows r WM .. r WM + WM - 1 of C (plain stores; the caller adds the rows up)
 };
+
+// K splits of a launch whose rows M only the device knows, over at most `wgs` workgroups: as many as give every live tile
+// that many compute units, at least 8 k-tiles each, none of them empty.  Splits store dense slices of `stride` elements.
+struct LiveSplits { int tiles, splits, per_split; long long stride; };
+constexpr int LIVE_TILE = 256, LIVE_WGS = 256;   // 256 x 256 tiles, one per compute unit
+__host__ __device__ inline LiveSplits live_splits(int M, int N, int K) {
+  LiveSplits r;
+  const int tm = (M + LIVE_TILE - 1) / LIVE_TILE, nk = (K + 63) / 64;
+  r.tiles = tm * ((N + LIVE_TILE - 1) / LIVE_TILE);
+  int s = r.tiles > 0 ? LIVE_WGS / r.tiles : 1;
+  s = s > nk / 8 ? nk / 8 : s;
+  s = s < 1 ? 1 : s;
+  r.per_split = (nk + s - 1) / s;
+  r.splits = r.per_split > 0 ? (nk + r.per_split - 1) / r.per_split : 0;
+  r.stride = (long long)tm * LIVE_TILE * N;
+  return r;
+}
 
 // Whether a launch takes the epilogue's 16-byte path (8 columns per lane); the kernels test it per launch, the host
 // tests it before it asks for EPI_COLSUM, which only that path provides.  C: the output of the batch entry.

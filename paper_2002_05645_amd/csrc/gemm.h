@@ -547,11 +547,15 @@ constexpr int dlds_lds_bytes() {
 }
 
 // EPI >= 0: the epilogue flags are this compile-time constant (the launcher guarantees g.epi == EPI), which takes
-// the flag tests and the code of the unused operations out of the unrolled epilogue; EPI < 0: flags read from g.epi.
+// the flag tests and the code of the unused operations out of the unrolled epilogue; EPI = -1: flags read from g.epi.
+// EPI = EPI_LIVE_SPLITS: fp32 partial results of a K split whose factor follows from the rows that *m_dev says are live
+// (live_splits): a grid of LIVE_WGS workgroups, of which tile count x splits have work, one tile each, no epilogue.
+constexpr int EPI_LIVE_SPLITS = -2;
 template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, typename TC, typename E = bf16, int EPI = -1>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_kernel(GemmArgs g) {
   constexpr int BK = 64;
-  const int epi = EPI >= 0 ? EPI : g.epi;
+  constexpr bool LIVE = EPI == EPI_LIVE_SPLITS;
+  const int epi = EPI >= 0 ? EPI : LIVE ? 0 : g.epi;
   const float alpha = EPI >= 0 ? 1.0f : g.alpha;   // the launcher sends only alpha = 1 to the kernels with compiled-in flags
   constexpr int NWM = BM / WM, NWN = BN / WN, NT = NWM * NWN * 64;
   constexpr int FM = WM / 32, FN = WN / 32, KK = BK / 16;
@@ -572,10 +576,22 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   if (g.k_dev) K = min(K, *g.k_dev);
   const int N = g.N;
 
-  const int tiles_n = (N + BN - 1) / BN, tiles_m = (g.M + BM - 1) / BM;
+  // (the tile order covers the live rows only, so that each XCD gets its share of them: with 4915 of 8192 rows live and
+  // the order over all rows, three of the eight XCDs had nothing to do)
+  const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM;
   const int nk_all = (K + BK - 1) / BK;
-  const int per_split = (nk_all + gridDim.y - 1) / gridDim.y;
-  const int kt0 = blockIdx.y * per_split, kt1 = min(nk_all, kt0 + per_split);
+  int first_tile = blockIdx.x, tile_step = gridDim.x, split = blockIdx.y, per_split = (nk_all + gridDim.y - 1) / gridDim.y;
+  long long split_stride = g.split_stride;
+  if constexpr (LIVE) {
+    const LiveSplits ls = live_splits(M, N, K);
+    if ((int)blockIdx.x >= ls.tiles * ls.splits) return;
+    first_tile = blockIdx.x % ls.tiles;
+    split = blockIdx.x / ls.tiles;
+    tile_step = ls.tiles;   // one tile
+    per_split = ls.per_split;
+    split_stride = ls.stride;
+  }
+  const int kt0 = split * per_split, kt1 = min(nk_all, kt0 + per_split);
   if (kt0 >= kt1) return;
 
   // A workgroup takes tiles blockIdx.x, blockIdx.x + gridDim.x, ...: launched with one workgroup per tile it runs
@@ -591,13 +607,13 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
     rb = make_rsrc(B, tile_bytes<BKC>(g.ldb, N - n0, K));
   };
   int staged_vb = -1;   // the tile whose first k-tile is already on its way into stage 0 (issued under the previous epilogue)
-  for (int vb = blockIdx.x; vb < tiles_m * tiles_n; vb += gridDim.x) {
+  for (int vb = first_tile; vb < tiles_m * tiles_n; vb += tile_step) {
   int tm, tn;
   tile_of_block(vb, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   if (m0 >= M) continue;
 
-  TC* C = (TC*)g.C + zo * g.c_zo + zi * g.c_zi + (long long)blockIdx.y * g.split_stride;
+  TC* C = (TC*)g.C + zo * g.c_zo + zi * g.c_zi + (long long)split * split_stride;
   __amdgpu_buffer_rsrc_t ra, rb;
   panels(m0, n0, ra, rb);
 
@@ -678,7 +694,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   __syncthreads();
 
   // ---- epilogue (as in gemm_mfma_kernel) ----------------------------------------------------------
-  const bool atomic = gridDim.y > 1 && g.split_stride == 0;
+  const bool atomic = !LIVE && gridDim.y > 1 && g.split_stride == 0;
   float* strip = (float*)(lds + STAGE + wave * EP_BYTES);   // behind stage 0, which the next tile is about to use
   const bool vec_ok = gemm_vec_ok(g, epi, C);
   // vector path: 8-column chunk and row-in-pass of this lane, its bias values, and the first pass's prefetch
@@ -720,7 +736,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   // The first k-tile of this workgroup's next tile goes into stage 0 now, under the epilogue (issued after the
   // epilogue's own first loads: loads return in order, and the passes must not wait for 64 KB of operands).
   {
-    const int vbn = vb + gridDim.x;
+    const int vbn = vb + tile_step;
     if (vbn < tiles_m * tiles_n) {
       int tmn, tnn;
       tile_of_block(vbn, tiles_m, tiles_n, tmn, tnn);

@@ -85,11 +85,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
   if (g.m_dev) M = min(M, *g.m_dev);
   if (g.k_dev) K = min(K, *g.k_dev);
   const int N = g.N;
-  const int tiles_n = (N + BN - 1) / BN, tiles_m = (g.M + BM - 1) / BM;
+  const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM;
+  if ((int)blockIdx.x >= tiles_m * tiles_n) return;   // (the tile order covers the live rows, dealt out over the XCDs)
   int tm, tn;
   tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  if (m0 >= M) return;
   const int nk_all = (K + BK - 1) / BK;
   const int per_split = (nk_all + gridDim.y - 1) / gridDim.y;
   const int kt0 = blockIdx.y * per_split, kt1 = min(nk_all, kt0 + per_split);

@@ -78,6 +78,19 @@ void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
       }
     }
   }
+  if constexpr (sizeof(TC) == 4 && BM == LIVE_TILE && BN == LIVE_TILE) {
+    if (g.live_splits) {   // A K-contiguous, B K-strided: the head's dX
+      constexpr int LDS = dlds_lds_bytes<BM, BN, WM, WN>();
+      auto kern = gemm_mfma_dlds_kernel<BM, BN, WM, WN, true, false, TC, E, EPI_LIVE_SPLITS>;
+      static const bool once = [&] {
+        (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        return true;
+      }();
+      (void)once;
+      hipLaunchKernelGGL(kern, dim3(LIVE_WGS), dim3((BM / WM) * (BN / WN) * 64), LDS, s, g);
+      return;
+    }
+  }
   if constexpr (BM < 128) {   // built for K-contiguous operands only: callers see to it
     launch_direct_one<BM, BN, WM, WN, true, true, TC, E>(g, s, splits);
   } else {

@@ -1073,6 +1073,31 @@ int embed_fwd_t(l2l_ctx* c, const int32_t* tokens, void* x_out) {
   });
 }
 
+// the head's dX = dz E for up to `rows` labelled rows, C left open
+GemmArgs head_dx_args(const l2l_ctx* c, int rows) {
+  const long long e_off = c->lay.eoff[E_E];
+  return gemm_args(rows, c->cfg.hidden, c->cfg.vocab, c->dz, c->Vp, 1, (const char*)c->emb + e_off * esize(c->cfg.dtype), c->cfg.hidden, 0,
+                   nullptr, c->cfg.hidden);
+}
+// elements of workspace that the K splits by live rows take at most
+size_t head_dx_live_elems(const GemmArgs& h) {
+  size_t most = 0;
+  for (int m = 1; m < h.M + LIVE_TILE; m += LIVE_TILE) {
+    const LiveSplits ls = live_splits(std::min(m, h.M), h.N, h.K);
+    most = std::max(most, (size_t)ls.splits * (size_t)ls.stride);
+  }
+  return most;
+}
+// whether they can be used: operands that the direct-to-LDS kernel takes, at least one whole tile each way, and no more
+// tiles than compute units (beyond that nothing is left to split)
+bool head_dx_live_shape_ok(const l2l_ctx* c, const GemmArgs& h) {
+  return is16(c->cfg.dtype) && !c->split_atomics && mfma_ok(h) && h.N % 8 == 0 && std::min(h.M, h.N) >= LIVE_TILE && h.K >= LIVE_TILE &&
+         live_splits(h.M, h.N, h.K).tiles <= LIVE_WGS;
+}
+bool head_dx_live_ok(const l2l_ctx* c, const GemmArgs& h) {
+  return head_dx_live_shape_ok(c, h) && c->split_ws && head_dx_live_elems(h) <= c->split_ws_elems;
+}
+
 template <typename T>
 int head_loss_t(l2l_ctx* c, const void* x_last, const int32_t* labels, void* dy_out, float* loss_out) {
   const l2l_config& f = c->cfg;
@@ -1123,20 +1148,32 @@ int head_loss_t(l2l_ctx* c, const void* x_last, const int32_t* labels, void* dy_
       else if (Vp <= 64 * CE_NT) go(ce_row_kernel<T, 16>, blocks, CE_NT);
       else go(ce_kernel<T>, (unsigned)rows, 256);
     }));
-    // dXl = dz E
+    // dXl = dz E: few tiles (rows x H) and a long contraction (the vocabulary).  How many rows are live only the device
+    // knows, so the kernel takes the K splits from there: all compute units work whatever the share of labelled rows, and
+    // one kernel adds the slices up and rounds.  (4915 of 8192 rows, H = 1024, V = 30522: 548 us with two splits fixed
+    // by the rows there is room for, atomics and two more kernels; 379 + 13 us this way.)
     if constexpr (sizeof(T) == 2) {
-      // few tiles (rows x H) and a long contraction (the vocabulary): as an accumulating fp32 GEMM into a cleared
-      // buffer it is split over K like the dW GEMMs, and rounded to the 16-bit format afterwards
-      L2L_TRY(fill_zero(c, c->dxl32, (size_t)rows * H * 4));
-      GemmArgs h = gemm_args(rows, H, V, c->dz, Vp, 1, E + eo[E_E], H, 0, c->dxl32, H);
+      GemmArgs h = head_dx_args(c, rows);
       h.m_dev = cnt;
-      h.epi = EPI_ACCUM;
-      L2L_TRY(gemm(c, dt, true, h, 0, L2L_PROF_OTHER));
-      const long long n = (long long)rows * H;
-      L2L_TRY(timed(c, L2L_PROF_OTHER, 0, 6.0 * n, [&] {
-        const unsigned blocks = (unsigned)std::min<long long>((n / 4 + 255) / 256 + 1, 2048);
-        hipLaunchKernelGGL(narrow_kernel<T>, dim3(blocks), dim3(256), 0, c->cs, c->dxl32, (T*)c->dxl, n);
-      }));
+      if (head_dx_live_ok(c, h)) {
+        h.C = c->split_ws;
+        h.live_splits = 1;
+        L2L_TRY(timed(c, L2L_PROF_OTHER, 2.0 * rows * H * (double)V, 0, [&] { launch_mfma_variant(6, h, c->cs, 1, true, dt == L2L_FP16); }));
+        L2L_TRY(timed(c, L2L_PROF_OTHER, 0, 0, [&] {
+          hipLaunchKernelGGL(live_sum_kernel<T>, dim3(1024), dim3(256), 0, c->cs, c->split_ws, cnt, rows, H, V, (T*)c->dxl);
+        }));
+      } else {
+        // as an accumulating fp32 GEMM into a cleared buffer it is split over K like the dW GEMMs, and rounded afterwards
+        L2L_TRY(fill_zero(c, c->dxl32, (size_t)rows * H * 4));
+        h.C = c->dxl32;
+        h.epi = EPI_ACCUM;
+        L2L_TRY(gemm(c, dt, true, h, 0, L2L_PROF_OTHER));
+        const long long n = (long long)rows * H;
+        L2L_TRY(timed(c, L2L_PROF_OTHER, 0, 6.0 * n, [&] {
+          const unsigned blocks = (unsigned)std::min<long long>((n / 4 + 255) / 256 + 1, 2048);
+          hipLaunchKernelGGL(narrow_kernel<T>, dim3(blocks), dim3(256), 0, c->cs, c->dxl32, (T*)c->dxl, n);
+        }));
+      }
     } else {
       GemmArgs h = gemm_args(rows, H, V, c->dz, Vp, 1, E + eo[E_E], H, 0, c->dxl, H);
       h.m_dev = cnt;
@@ -1318,29 +1355,6 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
   for (auto& b : bufs) L2L_TRY(dev_alloc(c, b.p, b.n * es));
   if (is16(cfg->dtype) && !c->no_weight_transpose)
     for (int i = 0; i < 2; ++i) L2L_TRY(dev_alloc(c, &c->wt[i], c->lay.total * es));
-  {   // workspace of the K-split GEMMs: the largest room that the layer's shapes ask for, within 64 MB (fp32: 32 MB)
-    const bool f32 = !is16(cfg->dtype);
-    const size_t most = (size_t)(f32 ? 8 : 16) << 20;
-    size_t need = 0;
-    const int h = cfg->hidden, f = cfg->ffn, m = (int)Mg;
-    const int shapes[][3] = {{m, 3 * h, h}, {m, h, h}, {m, f, h}, {m, h, f}, {m, h, 3 * h}, {h, 3 * h, m}, {h, h, m}, {h, f, m}, {f, h, m}};
-    for (int i = 0; i < 9; ++i) {
-      const auto& s = shapes[i];
-      const int kc = i < 5;   // the last four are the dW shapes
-      GemmArgs g = gemm_args(s[0], s[1], s[2], nullptr, kc ? s[2] : s[0], kc, nullptr, kc ? s[2] : s[1], kc, nullptr, s[1]);
-      if (!kc) g.epi = EPI_ACCUM;
-      int v = 0, splits = 1;
-      if (f32) splits = pick_f32_splits(g, most);
-      else choose_tile(g, !kc, most, &v, &splits);
-      if (splits > 1) need = std::max(need, (size_t)splits * s[0] * s[1]);
-    }
-    if (const char* e = getenv("L2L_SPLIT_WS_MB")) need = (size_t)atoll(e) << 18;   // tuning: room for other split factors
-    if (need == 0 && !f32) need = 64;   // (the 16-bit launches choose their tile by time where a workspace exists)
-    if (need > 0) {
-      c->split_ws_elems = need;
-      L2L_TRY(dev_alloc(c, (void**)&c->split_ws, need * 4));
-    }
-  }
   if (is16(cfg->dtype)) {   // partial column sums out of a GEMM epilogue: one row per 64 rows of the group at most
     c->colsum_ws_elems = (size_t)((Mg + 63) / 64) * std::max(F, 3 * H);
     L2L_TRY(dev_alloc(c, (void**)&c->colsum_ws, c->colsum_ws_elems * 4));
@@ -1374,7 +1388,6 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
     L2L_TRY(dev_alloc(c, (void**)&c->chunk_cnt, ((UT + c->head_rows - 1) / c->head_rows) * 4));
     L2L_TRY(dev_alloc(c, &c->xl, c->head_rows * H * es));
     L2L_TRY(dev_alloc(c, &c->dxl, c->head_rows * H * es));
-    if (is16(cfg->dtype)) L2L_TRY(dev_alloc(c, (void**)&c->dxl32, c->head_rows * H * 4));
     L2L_TRY(dev_alloc(c, (void**)&c->logits, c->head_rows * c->Vp * 4));
     L2L_TRY(dev_alloc(c, &c->dz, c->head_rows * c->Vp * es));
     HIP_TRY(c, hipEventCreateWithFlags(&c->emb_staged_ev, hipEventDisableTiming));
@@ -1382,6 +1395,38 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
     HIP_TRY(c, hipEventCreateWithFlags(&c->egacc_ready, hipEventDisableTiming));
     HIP_TRY(c, hipEventCreateWithFlags(&c->egacc_drained, hipEventDisableTiming));
     HIP_TRY(c, hipEventCreateWithFlags(&c->egacc_landed, hipEventDisableTiming));
+  }
+  {   // workspace of the K-split GEMMs: the largest room that the layer's shapes ask for, within 64 MB (fp32: 32 MB)
+    const bool f32 = !is16(cfg->dtype);
+    const size_t most = (size_t)(f32 ? 8 : 16) << 20;
+    size_t need = 0;
+    const int h = cfg->hidden, f = cfg->ffn, m = (int)Mg;
+    const int shapes[][3] = {{m, 3 * h, h}, {m, h, h}, {m, f, h}, {m, h, f}, {m, h, 3 * h}, {h, 3 * h, m}, {h, h, m}, {h, f, m}, {f, h, m}};
+    for (int i = 0; i < 9; ++i) {
+      const auto& s = shapes[i];
+      const int kc = i < 5;   // the last four are the dW shapes
+      GemmArgs g = gemm_args(s[0], s[1], s[2], nullptr, kc ? s[2] : s[0], kc, nullptr, kc ? s[2] : s[1], kc, nullptr, s[1]);
+      if (!kc) g.epi = EPI_ACCUM;
+      int v = 0, splits = 1;
+      if (f32) splits = pick_f32_splits(g, most);
+      else choose_tile(g, !kc, most, &v, &splits);
+      if (splits > 1) need = std::max(need, (size_t)splits * s[0] * s[1]);
+    }
+    if (cfg->vocab > 0 && !f32) {
+      const GemmArgs h = head_dx_args(c, (int)c->head_rows);
+      if (head_dx_live_shape_ok(c, h)) need = std::max(need, head_dx_live_elems(h));
+    }
+    if (const char* e = getenv("L2L_SPLIT_WS_MB")) need = (size_t)atoll(e) << 18;   // tuning: room for other split factors
+    if (need == 0 && !f32) need = 64;   // (the 16-bit launches choose their tile by time where a workspace exists)
+    if (need > 0) {
+      c->split_ws_elems = need;
+      L2L_TRY(dev_alloc(c, (void**)&c->split_ws, need * 4));
+    }
+  }
+  if (cfg->vocab > 0 && is16(cfg->dtype)) {   // the passes of the head that split their dX another way sum into a buffer of fp32
+    const GemmArgs last = head_dx_args(c, (int)((c->T * cfg->num_ubatches - 1) % c->head_rows + 1));
+    if (!head_dx_live_ok(c, head_dx_args(c, (int)c->head_rows)) || !head_dx_live_ok(c, last))
+      L2L_TRY(dev_alloc(c, (void**)&c->dxl32, c->head_rows * H * 4));
   }
   return L2L_OK;
 }

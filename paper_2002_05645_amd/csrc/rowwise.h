@@ -838,6 +838,25 @@ __global__ __launch_bounds__(256) void split_epilogue_kernel(const float* part, 
   }
 }
 
+// out[m, :] = sum of the slices of a live_splits GEMM (*cnt live rows of n columns, contraction over K), rounded to E;
+// n a multiple of 8, out dense.
+template <typename E>
+__global__ __launch_bounds__(256) void live_sum_kernel(const float* part, const int* cnt, int rows, int n, int K, E* out) {
+  const int M = min(rows, *cnt);
+  const LiveSplits ls = live_splits(M, n, K);
+  const long long total = (long long)M * n / 8;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+    float v[8], t[8];
+    load8(part + 8 * i, v);
+    for (int k = 1; k < ls.splits; ++k) {
+      load8(part + k * ls.stride + 8 * i, t);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += t[e];
+    }
+    store8(out + 8 * i, v);
+  }
+}
+
 // p[i] = v for i < n (a kernel rather than a memset so that callers can capture it in a graph).
 // 16-byte stores over the aligned body, dwords for the tail.
 __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* p, uint32_t v, long long n) {

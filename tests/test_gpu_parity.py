@@ -1145,3 +1145,12 @@ def test_head_vocabulary_sizes(vocab, dtype):
     # the loop over memory beyond 32768
     errs = _head_case(vocab, 64, 3, 24, dtype, 0.7, vocab)
     assert all(e <= HEAD_TOL[dtype] for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("vocab,hidden,seqs,label_prob", [(1000, 256, 5, 1.0), (5002, 264, 10, 0.001), (5002, 1032, 40, 0.3), (9000, 512, 33, 0.9)])
+def test_head_dx_split_by_live_rows(vocab, hidden, seqs, label_prob, dtype):
+    # the K splits of the head's dX follow from the live rows: one row, a few tiles of many, all of them; edge tiles in
+    # both directions
+    errs = _head_case(vocab, hidden, seqs, 104, dtype, label_prob, vocab + hidden)
+    assert all(e <= HEAD_TOL[dtype] for e in errs.values()), errs

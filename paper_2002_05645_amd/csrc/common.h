@@ -207,6 +207,7 @@ struct GemmArgs {
   int resident;           // direct-to-LDS kernel: > 0 = launch at most this many workgroups (one per compute unit) and let
                           // each walk its share of the tile order; 0 = one workgroup per tile
   int live_splits;        // 1: K splits by live_splits(*m_dev, N, K), partial results to C (256 x 256 tiles, A K-contiguous, B K-strided)
+  int fresh;              // EPI_ACCUM: 1 = C holds no sum yet, its content counts as zero and need not be
   float* colsum;          // EPI_COLSUM: fp32 [ceil(M / WM)][N] (WM = rows of a wave's tile): row r receives the column sums
                           // of the values stored to rows r WM .. r WM + WM - 1 of C (plain stores; the caller adds the rows up)
 };

@@ -801,10 +801,10 @@ __global__ __launch_bounds__(256) void narrow_kernel(const float* in, E* out, lo
   for (long long i = n4 * 4 + (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) out[i] = from_f32<E>(in[i]);
 }
 
-// Sum of the K-split partial results of a GEMM: out[m, n] += sum_s part[s][m, n] (part: `splits` dense [rows, n]
+// Sum of the K-split partial results of a GEMM: out[m, n] += sum_s part[s][m, n], or = where `fresh` (part: `splits` dense [rows, n]
 // fp32 matrices, n a multiple of 4; out: row stride ldo, 16-byte aligned rows).
 __global__ __launch_bounds__(256) void split_sum_kernel(const float* part, int splits, long long rows, int n, float* out,
-                                                        long long ldo) {
+                                                        long long ldo, int fresh) {
   const long long total4 = rows * n / 4, slice = rows * n;
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total4; i += (long long)gridDim.x * 256) {
     const long long e = i * 4, r = e / n;
@@ -812,7 +812,7 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* part, int s
     f32x4 s = *(const f32x4*)(part + e);
     for (int k = 1; k < splits; ++k) s += *(const f32x4*)(part + k * slice + e);
     f32x4* o = (f32x4*)(out + r * ldo + col);
-    *o = *o + s;
+    *o = fresh ? s : *o + s;
   }
 }
 
@@ -855,6 +855,14 @@ __global__ __launch_bounds__(256) void live_sum_kernel(const float* part, const 
     }
     store8(out + 8 * i, v);
   }
+}
+
+// clears up to four ranges of p ([first, first + count), multiples of four elements each), one grid row per range
+struct ClearRanges { long long first[4], count[4]; };
+__global__ __launch_bounds__(256) void clear_ranges_kernel(float* p, ClearRanges r) {
+  const int k = blockIdx.y;
+  f32x4* q = (f32x4*)(p + r.first[k]);
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < r.count[k] / 4; i += (long long)gridDim.x * 256) q[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 // p[i] = v for i < n (a kernel rather than a memset so that callers can capture it in a graph).

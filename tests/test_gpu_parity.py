@@ -1154,3 +1154,37 @@ def test_head_dx_split_by_live_rows(vocab, hidden, seqs, label_prob, dtype):
     # both directions
     errs = _head_case(vocab, hidden, seqs, 104, dtype, label_prob, vocab + hidden)
     assert all(e <= HEAD_TOL[dtype] for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("switch", [None, "L2L_SPLIT_ATOMICS", "L2L_GEMM_RESIDENT"])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("group", [1, 3])
+def test_layer_gradients_do_not_depend_on_what_the_accumulator_held(monkeypatch, group, dtype, switch):
+    # an accumulator's matrices are not cleared between its users: the first group of a visit stores over them, the
+    # others add; four visits take either accumulator twice, with different upstream gradients in between
+    if switch:
+        monkeypatch.setenv(switch, "1" if switch == "L2L_SPLIT_ATOMICS" else "0")
+    H, seq = 136, 40
+    cfg = P.make_config(H, 1, 264, seq, 2, 3, dtype, 1e-12, 0, group)
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    total = P.lib().l2l_layer_packed_elems(cfg)
+    c = P.Context(cfg)
+    host = (torch.randn(total, device="cuda", generator=gen) * 0.05).to(dt).cpu().pin_memory()
+    c.param_stage(0, host, 0)
+    x = torch.randn((3, 2, seq, H), device="cuda", generator=gen).to(dt)
+    dys = [(torch.randn(x.shape, device="cuda", generator=gen) * f).to(dt) for f in (1.0, 100.0)]
+    lands = []
+    for visit in range(4):
+        dy, land = dys[visit // 2 % 2 if visit else 0].clone(), torch.zeros(total).pin_memory()
+        if visit == 3:
+            dy = dys[0].clone()
+        c.layer_bwd(0, 0, x, dy)
+        c.grad_drain(0, land)
+        c.sync()
+        lands.append(land)
+    c.close()
+    rel = lambda a, b: float((a - b).norm() / b.norm())
+    # fp32 sums in another order (atomics) at most: a few units in the last place
+    assert rel(lands[1], lands[0]) < 1e-5 and rel(lands[3], lands[0]) < 1e-5
+    assert rel(lands[2], lands[0]) > 10

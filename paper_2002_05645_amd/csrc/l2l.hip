@@ -1233,6 +1233,26 @@ int embed_bwd_t(l2l_ctx* c, const int32_t* tokens, const void* dy) {
   const T* E = (const T*)c->emb;
   const long long* eo = c->lay.eoff;
   const int H = c->cfg.hidden, S = c->cfg.seq;
+  if (H <= 2048) {   // (the registers of one wave hold four groups of 512 columns)
+    // sequences per block: many, so that few blocks add into the same dgamma and dbeta, as long as 1024 blocks (four per
+    // compute unit) remain; fewer than 16 where those would leave compute units idle
+    const long long nseq = rows / S;
+    int seqs = 16;
+    while (seqs < 64 && S * ((nseq + 2 * seqs - 1) / (2 * seqs)) >= 1024) seqs *= 2;
+    while (seqs > 4 && S * ((nseq + seqs - 1) / seqs) < 256) seqs /= 2;
+    const int nch = (H + 511) / 512;
+    return timed(c, L2L_PROF_ROWWISE, 0, 2.0 * rows * H * sizeof(T), [&] {
+      const auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)(S * ((nseq + seqs - 1) / seqs))), dim3(256), (size_t)4 * nch * 512 * sizeof(float), c->cs, tokens,
+                           E + eo[E_E], E + eo[E_P], E + eo[E_GE], (const T*)dy, c->emean, c->erstd, c->egacc + eo[E_E], c->egacc + eo[E_P],
+                           c->egacc + eo[E_GE], c->egacc + eo[E_BE], (int)rows, S, H, c->cfg.vocab, seqs);
+      };
+      if (nch == 1) go(embed_bwd_fused_kernel<T, 1>);
+      else if (nch == 2) go(embed_bwd_fused_kernel<T, 2>);
+      else if (nch == 3) go(embed_bwd_fused_kernel<T, 3>);
+      else go(embed_bwd_fused_kernel<T, 4>);
+    });
+  }
   L2L_TRY(timed(c, L2L_PROF_ROWWISE, 0, 0, [&] {
     const unsigned nseq = (unsigned)(rows / S);
     const bool turned = (size_t)5 * H * sizeof(float) <= (size_t)128 << 10;   // room for a row per wave in LDS

@@ -1090,7 +1090,8 @@ def test_call_order_errors():
 
 
 def _head_case(vocab, hidden, seqs, seq, dtype, label_prob, seed):
-    """loss, dL/dX, dE and dbv of the LM head against the same in 64 bits; returns their relative errors"""
+    """loss and dL/dX of the LM head, and the gradients of the embedding block, against the same in 64 bits; returns their
+    relative errors"""
     cfg = P.make_config(hidden, 1, 64, seq, seqs, 1, dtype, 1e-12, vocab=vocab)
     gen = torch.Generator(device="cuda").manual_seed(seed)
     dt = {"fp32": torch.float32, "bf16": torch.bfloat16, "fp16": torch.float16}[dtype]
@@ -1108,10 +1109,11 @@ def _head_case(vocab, hidden, seqs, seq, dtype, label_prob, seed):
     dy, loss = torch.empty_like(x), torch.zeros(1, device="cuda")
     if dtype == "fp16":
         c.set_loss_scale(1024.0)
-    tok = torch.zeros((1, seqs, seq), dtype=torch.int32, device="cuda")
+    tok = torch.randint(0, vocab, (1, seqs, seq), dtype=torch.int32, device="cuda", generator=gen)
+    dx0 = (torch.randn(x.shape, device="cuda", generator=gen) * 0.01).to(dt)
     c.embed_fwd(tok, torch.empty_like(x))
     c.head_loss(x, lab, dy, loss)
-    c.embed_bwd(tok, torch.zeros_like(x))
+    c.embed_bwd(tok, dx0)
     land = torch.zeros(total).pin_memory()
     c.embed_grad_drain(land)
     c.sync()
@@ -1129,9 +1131,13 @@ def _head_case(vocab, hidden, seqs, seq, dtype, label_prob, seed):
     dz *= scale / len(ll)
     dx = torch.zeros(rows, hidden, dtype=torch.float64, device="cuda")
     dx[live] = dz @ E
-    rel = lambda a, b: float((a.double().cpu().view(-1) - b.cpu().view(-1)).norm() / b.norm())
-    return {"loss": abs(float(loss) - float(ref_loss)) / abs(float(ref_loss)), "dx": rel(dy, dx),
-            "dE": rel(land[layout["E"][0]:][:vocab * hidden], dz.t() @ xl), "dbv": rel(land[layout["bv"][0]:][:vocab], dz.sum(0))}
+    t = {k: block[layout[k][0]:][:layout[k][1]].double().requires_grad_() for k in ("E", "P", "ge", "be")}
+    emb = t["E"].view(vocab, hidden)[tok.view(-1).long()].view(seqs, seq, hidden) + t["P"].view(seq, hidden)
+    torch.nn.functional.layer_norm(emb, (hidden,), t["ge"], t["be"], 1e-12).backward(dx0[0].double())
+    rel = lambda a, b: float((a.double().cpu().view(-1) - b.cpu().reshape(-1)).norm() / b.norm())
+    got = {k: land[layout[k][0]:][:layout[k][1]] for k in t}
+    return {"dP": rel(got["P"], t["P"].grad), "dge": rel(got["ge"], t["ge"].grad), "dbe": rel(got["be"], t["be"].grad), "loss": abs(float(loss) - float(ref_loss)) / abs(float(ref_loss)), "dx": rel(dy, dx),
+            "dE": rel(got["E"], dz.t() @ xl + t["E"].grad.view(vocab, hidden)), "dbv": rel(land[layout["bv"][0]:][:vocab], dz.sum(0))}
 
 
 # dz and dX are rounded once each to the format (2^-9 of a value for bf16, 2^-12 for fp16, at most), sums are in fp32
@@ -1188,3 +1194,12 @@ def test_layer_gradients_do_not_depend_on_what_the_accumulator_held(monkeypatch,
     # fp32 sums in another order (atomics) at most: a few units in the last place
     assert rel(lands[1], lands[0]) < 1e-5 and rel(lands[3], lands[0]) < 1e-5
     assert rel(lands[2], lands[0]) > 10
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("hidden,seqs,seq", [(8, 1, 8), (512, 3, 64), (520, 65, 16), (1024, 70, 24), (1536, 17, 8), (1544, 5, 40), (2048, 130, 16), (2056, 6, 16)])
+def test_embedding_backward_widths_and_sequences_per_block(hidden, seqs, seq, dtype):
+    # 1 to 4 column groups of 512 in registers and their edges, rows beyond 2048 columns in the two-kernel form; one
+    # sequence, blocks that end inside a wave's share, 4 to 64 sequences per block
+    errs = _head_case(500, hidden, seqs, seq, dtype, 0.5, hidden + seqs)
+    assert all(e <= HEAD_TOL[dtype] for e in errs.values()), errs

@@ -91,6 +91,14 @@ void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
       return;
     }
   }
+  // fp32 output: the partial results of K splits and a dW that is stored (no flag), and the logits (bias)
+  if constexpr (sizeof(TC) == 4) {
+    if (g.alpha == 1.0f && g.a_kc && g.b_kc && g.epi == 0) { launch_direct_one<BM, BN, WM, WN, true, true, TC, E, 0>(g, s, splits); return; }
+    if constexpr (BM >= 128)
+      if (g.alpha == 1.0f && !g.a_kc && !g.b_kc && g.epi == 0) { launch_direct_one<BM, BN, WM, WN, false, false, TC, E, 0>(g, s, splits); return; }
+    if constexpr (BM == 256 && BN == 256)
+      if (g.alpha == 1.0f && g.a_kc && g.b_kc && g.epi == EPI_BIAS) { launch_direct_one<BM, BN, WM, WN, true, true, TC, E, EPI_BIAS>(g, s, splits); return; }
+  }
   if constexpr (BM < 128) {   // built for K-contiguous operands only: callers see to it
     launch_direct_one<BM, BN, WM, WN, true, true, TC, E>(g, s, splits);
   } else {

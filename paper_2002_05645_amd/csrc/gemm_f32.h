@@ -4,8 +4,9 @@
 
 // Block tile 64 x 64, k-tiles of 32, four waves of 32 x 32.  Bound by the matrix cores: a k-tile's 16 products take a SIMD
 // 1024 clocks and its operands are 16 KB, half of what a compute unit can load meanwhile.  So nothing elaborate feeds
-// them: a k-tile goes global -> registers -> LDS, one k-tile ahead, in two stages of 18 KB, and the other workgroups of
-// the unit (four fit) cover the waits.  (A 128 x 128 tile, two workgroups per unit, took 257 us where this one takes 185
+// them: a k-tile goes global -> registers -> LDS, requested two k-tiles ahead (a k-tile's products take half of what a load
+// from memory does; one ahead the layer of width 768 took 2443 us, two ahead 2281, a step of the tiny model 1265 and 1140), in two
+// stages of 18 KB, and the other workgroups of the unit (four fit) cover the waits.  (A 128 x 128 tile, two workgroups per unit, took 257 us where this one takes 185
 // at 19.3 GFLOP: three of its workgroups per unit leave the last one alone with its own waits.)
 // The order of the contraction index is free as long as both operands agree: lane half h supplies k = 8 s + 4 h + j in
 // product j of step s, which lets a K-contiguous operand be read from its [row][32] image as one 16-byte fragment per
@@ -104,22 +105,29 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, TA::bytes(g.lda, M - m0, K));
     const __amdgpu_buffer_rsrc_t rb = make_rsrc(B, TB::bytes(g.ldb, N - n0, K));
     const uint32_t lda = (uint32_t)g.lda, ldb = (uint32_t)g.ldb;
-    TA ta;
-    TB tb;
-    ta.load(ra, lda, kt0 * BK, K, tid);
-    tb.load(rb, ldb, kt0 * BK, K, tid);
-    ta.store(ldsf, tid);
-    tb.store(ldsf + TA::FLOATS, tid);
+    TA ta[2];
+    TB tb[2];
+    const auto load = [&](auto pc, int kt) {
+      constexpr int P = decltype(pc)::value;
+      ta[P].load(ra, lda, kt * BK, K, tid);
+      tb[P].load(rb, ldb, kt * BK, K, tid);
+    };
+    const auto store = [&](auto pc) {   // register set P goes to stage P
+      constexpr int P = decltype(pc)::value;
+      ta[P].store(ldsf + P * STAGE, tid);
+      tb[P].store(ldsf + P * STAGE + TA::FLOATS, tid);
+    };
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    load(even, kt0);
+    if (kt0 + 1 < kt1) load(odd, kt0 + 1);
+    store(even);
     __syncthreads();
     const int arow = wm * 32 + (lane & 31), brow = wn * 32 + (lane & 31);
-    for (int kt = kt0; kt < kt1; ++kt) {
-      const float* cur = ldsf + ((kt - kt0) & 1) * STAGE;
-      float* nxt = ldsf + ((kt - kt0 + 1) & 1) * STAGE;
-      const bool more = kt + 1 < kt1;
-      if (more) {
-        ta.load(ra, lda, (kt + 1) * BK, K, tid);
-        tb.load(rb, ldb, (kt + 1) * BK, K, tid);
-      }
+    const auto step = [&](auto pc, int kt) {
+      constexpr int P = decltype(pc)::value;
+      const float* cur = ldsf + P * STAGE;
+      if (kt + 2 < kt1) load(pc, kt + 2);   // (set P held k-tile kt, which is in LDS)
       static_for<0, BK / 8>([&](auto sc) {
         constexpr int s = decltype(sc)::value;
         const f32x4 af = TA::frag(cur, arow, s, lane), bf = TB::frag(cur + TA::FLOATS, brow, s, lane);
@@ -128,11 +136,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
           acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[e], bf[e], acc, 0, 0, 0);
         });
       });
-      if (more) {   // (the other stage was last read before the previous barrier)
-        ta.store(nxt, tid);
-        tb.store(nxt + TA::FLOATS, tid);
-      }
+      if (kt + 1 < kt1) store(std::integral_constant<int, P ^ 1>{});   // (the other stage was last read before the previous barrier)
       __syncthreads();
+    };
+    for (int kt = kt0; kt < kt1; kt += 2) {
+      step(even, kt);
+      if (kt + 1 < kt1) step(odd, kt + 1);
     }
   }
   // Register r of a lane: row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32.  What the epilogue reads is asked for

@@ -34,11 +34,11 @@ void launch_layout(const GemmArgs& g, hipStream_t s, int splits) {
 
 }  // namespace
 
-template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, typename TC, typename E, int EPI = -1>
+template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, typename TC, typename E, int NST, int EPI = -1>
 void launch_direct_one(const GemmArgs& g, hipStream_t s, int splits) {
-  constexpr int LDS = dlds_lds_bytes<BM, BN, WM, WN>();
+  constexpr int LDS = dlds_lds_bytes<BM, BN, WM, WN, NST>();
   static_assert(LDS <= 160 * 1024, "tile does not fit the 160 KB LDS");
-  auto kern = gemm_mfma_dlds_kernel<BM, BN, WM, WN, AKC, BKC, TC, E, EPI>;
+  auto kern = gemm_mfma_dlds_kernel<BM, BN, WM, WN, AKC, BKC, TC, E, EPI, NST>;
   static const bool once = [&] {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     return true;
@@ -56,7 +56,7 @@ void launch_direct_one(const GemmArgs& g, hipStream_t s, int splits) {
 
 // the direct-to-LDS kernel is built for the two layout pairs that carry the layer's work: both operands
 // K-contiguous (forward with transposed weights, dX) and both K-strided (dW)
-template <int BM, int BN, int WM, int WN, typename TC, typename E>
+template <int BM, int BN, int WM, int WN, typename TC, typename E, int NST>
 void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
   // 16-bit output and both operands K-contiguous: the layer's forward, recompute and dX GEMMs.  Their eight epilogues
   // get kernels with the flags compiled in (a third off the epilogue's time); any other combination runs the kernel
@@ -64,7 +64,7 @@ void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
   if constexpr (sizeof(TC) == 2) {
     if (g.a_kc && g.b_kc && g.alpha == 1.0f) {
       switch (g.epi) {
-#define L2L_EPI_CASE(e) case (e): launch_direct_one<BM, BN, WM, WN, true, true, TC, E, (e)>(g, s, splits); return;
+#define L2L_EPI_CASE(e) case (e): launch_direct_one<BM, BN, WM, WN, true, true, TC, E, NST, (e)>(g, s, splits); return;
         L2L_EPI_CASE(0)
         L2L_EPI_CASE(EPI_BIAS)
         L2L_EPI_CASE(EPI_BIAS | EPI_RESID)
@@ -93,18 +93,18 @@ void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
   }
   // fp32 output: the partial results of K splits and a dW that is stored (no flag), and the logits (bias)
   if constexpr (sizeof(TC) == 4) {
-    if (g.alpha == 1.0f && g.a_kc && g.b_kc && g.epi == 0) { launch_direct_one<BM, BN, WM, WN, true, true, TC, E, 0>(g, s, splits); return; }
+    if (g.alpha == 1.0f && g.a_kc && g.b_kc && g.epi == 0) { launch_direct_one<BM, BN, WM, WN, true, true, TC, E, NST, 0>(g, s, splits); return; }
     if constexpr (BM >= 128)
-      if (g.alpha == 1.0f && !g.a_kc && !g.b_kc && g.epi == 0) { launch_direct_one<BM, BN, WM, WN, false, false, TC, E, 0>(g, s, splits); return; }
+      if (g.alpha == 1.0f && !g.a_kc && !g.b_kc && g.epi == 0) { launch_direct_one<BM, BN, WM, WN, false, false, TC, E, NST, 0>(g, s, splits); return; }
     if constexpr (BM == 256 && BN == 256)
-      if (g.alpha == 1.0f && g.a_kc && g.b_kc && g.epi == EPI_BIAS) { launch_direct_one<BM, BN, WM, WN, true, true, TC, E, EPI_BIAS>(g, s, splits); return; }
+      if (g.alpha == 1.0f && g.a_kc && g.b_kc && g.epi == EPI_BIAS) { launch_direct_one<BM, BN, WM, WN, true, true, TC, E, NST, EPI_BIAS>(g, s, splits); return; }
   }
   if constexpr (BM < 128) {   // built for K-contiguous operands only: callers see to it
-    launch_direct_one<BM, BN, WM, WN, true, true, TC, E>(g, s, splits);
+    launch_direct_one<BM, BN, WM, WN, true, true, TC, E, NST>(g, s, splits);
   } else {
-    if (g.a_kc && g.b_kc) launch_direct_one<BM, BN, WM, WN, true, true, TC, E>(g, s, splits);
-    else if (g.a_kc) launch_direct_one<BM, BN, WM, WN, true, false, TC, E>(g, s, splits);
-    else launch_direct_one<BM, BN, WM, WN, false, false, TC, E>(g, s, splits);
+    if (g.a_kc && g.b_kc) launch_direct_one<BM, BN, WM, WN, true, true, TC, E, NST>(g, s, splits);
+    else if (g.a_kc) launch_direct_one<BM, BN, WM, WN, true, false, TC, E, NST>(g, s, splits);
+    else launch_direct_one<BM, BN, WM, WN, false, false, TC, E, NST>(g, s, splits);
   }
 }
 
@@ -128,8 +128,8 @@ typedef bf16 Elem;
 
 void L2L_LAUNCH_NAME(const GemmArgs& g, hipStream_t s, int splits, bool out_f32) {
   if constexpr (kThis.direct) {   // callers pick these variants for every layout pair but (A K-strided, B K-contiguous)
-    if (out_f32) launch_direct<kThis.bm, kThis.bn, kThis.wm, kThis.wn, float, Elem>(g, s, splits);
-    else launch_direct<kThis.bm, kThis.bn, kThis.wm, kThis.wn, Elem, Elem>(g, s, 1);
+    if (out_f32) launch_direct<kThis.bm, kThis.bn, kThis.wm, kThis.wn, float, Elem, kThis.direct + 1>(g, s, splits);
+    else launch_direct<kThis.bm, kThis.bn, kThis.wm, kThis.wn, Elem, Elem, kThis.direct + 1>(g, s, 1);
   } else {
     if (out_f32) launch_layout<kThis.bm, kThis.bn, kThis.bk, kThis.wm, kThis.wn, float, Elem>(g, s, splits);
     else launch_layout<kThis.bm, kThis.bn, kThis.bk, kThis.wm, kThis.wn, Elem, Elem>(g, s, 1);

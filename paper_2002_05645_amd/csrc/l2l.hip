@@ -327,7 +327,8 @@ bool mfma_ok(const GemmArgs& g) {
   if (g.a_kc && g.b_kc && g.K % 8) return false;  // nobody guarantees zero padding in both
   // The kernels address an operand panel through a 32-bit buffer descriptor, with 0x80000000 as the offset that is
   // out of range for sure: every panel (one batch entry's operand, seen from its first element) must end below
-  // 2 GiB, and the offsets of the K-strided loads that run up to three k-tiles past the end must not wrap.
+  // 2 GiB, and the offsets of the K-strided loads must not wrap (they run up to four k-tiles past the end, where a panel
+  // that ends below 2 GiB with three k-tiles to spare leaves room for many more).
   const long long lim = (1LL << 31) - 1;
   const long long ea = g.a_kc ? (long long)(g.M - 1) * g.lda + k8 : (long long)(g.K + 192) * g.lda + m8;
   const long long eb = g.b_kc ? (long long)(g.N - 1) * g.ldb + k8 : (long long)(g.K + 192) * g.ldb + n8;
@@ -467,9 +468,12 @@ int variant_for_layout(int v, const GemmArgs& g) {
 // 242 us against 308 on 256 x 128, 322 on 128 x 128, 460 on 64 x 64); below that the smaller tiles win as soon as it
 // leaves units idle (4096 x 1024 x 4096: 80 us on 64 of its tiles, 50 to 56 on 256 of 128 x 128; 64 x 1024 x 4096: 71
 // against 20 us on 64 x 64).  K splits go through the workspace and cost a second launch and the traffic of their
-// partial sums.
+// partial sums.  The 128 x 128 tile with three LDS stages (variant 4; K-contiguous operands) is for one workgroup per unit:
+// 4096 x 1024 x 4096 takes 41.8 us against 51.6 with two stages, 4096 x 4096 x 1024, four workgroups per unit, 56.4
+// against 41.6.  Both operands K-strided it gains nothing (66.4 against 66.7 us at 1024 x 4096 x 4096: bound by LDS reads).
 struct TileCost { int v; double busy, lone_few, lone_all, rest; int together; };
-constexpr TileCost kCostKC[] = {{5, 0.225, 0.30, 0.47, 1.5, 4}, {7, 0.60, 0.60, 0.70, 3.0, 2}, {8, 0.97, 0.80, 0.97, 4.5, 1}, {6, 1.58, 1.05, 1.58, 5.8, 1}};
+constexpr TileCost kCostKC[] = {{5, 0.225, 0.30, 0.47, 1.5, 4}, {7, 0.60, 0.66, 0.74, 3.0, 2}, {4, 0.69, 0.46, 0.60, 3.0, 1}, {8, 0.88, 0.57, 0.88, 4.5, 1},
+                                {6, 1.58, 1.05, 1.58, 5.8, 1}};
 // both operands K-strided (dW)
 constexpr TileCost kCostKS[] = {{7, 0.66, 0.92, 1.12, 6.0, 2}, {8, 1.42, 1.14, 1.42, 7.0, 1}, {6, 2.20, 1.70, 2.20, 10.0, 1}};
 
@@ -478,7 +482,7 @@ void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant,
   const bool colsum = (g.epi & EPI_COLSUM) != 0, accum = out_f32 && g.epi == EPI_ACCUM;
   const bool can_split = split_epilogue_ok(g);
   const TileCost* cost = g.a_kc ? kCostKC : kCostKS;
-  const int ncost = g.a_kc ? 4 : 3;
+  const int ncost = g.a_kc ? 5 : 3;
   const int nk = std::max(1, (g.K + 63) / 64);
   double best = 1e300;
   for (int i = 0; i < ncost; ++i) {

@@ -1203,3 +1203,16 @@ def test_embedding_backward_widths_and_sequences_per_block(hidden, seqs, seq, dt
     # sequence, blocks that end inside a wave's share, 4 to 64 sequences per block
     errs = _head_case(500, hidden, seqs, seq, dtype, 0.5, hidden + seqs)
     assert all(e <= HEAD_TOL[dtype] for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("variant", [4, 8])
+@pytest.mark.parametrize("K", [8, 64, 72, 136, 200, 264, 328])
+def test_gemm_three_stage_tiles_k_tile_counts(ctx, variant, K):
+    # one to six k-tiles through three LDS stages (loads run up to three k-tiles past the end), every layout pair the
+    # kernel has; 256 x 128 tiles also walked by resident workgroups (21 x 21 tiles, more than compute units)
+    impl = 100 + variant
+    assert _gemm_case(ctx, "bf16", impl, 1, 1, 264, 392, K, bias=True, pad=8) < OUT16["bf16"]
+    assert _gemm_case(ctx, "bf16", impl, 1, 0, 264, 392, K, out_f32=True, pad=8) < 2e-6
+    assert _gemm_case(ctx, "fp16", impl, 0, 0, 264, 392, K, out_f32=True, pad=8) < 2e-6
+    if variant == 8:
+        assert _gemm_case(ctx, "bf16", impl, 1, 1, 5200, 2600, K, resid=True, pad=8) < OUT16["bf16"]

@@ -14,7 +14,7 @@
 // (pitch rows + 8: the two lane halves on different banks).  No operand is transposed, whatever its layout in memory.
 // Results leave straight from the accumulators: a register holds 32 consecutive columns of two rows, which are whole
 // 128-byte segments in fp32.
-// Measured (4096 tokens of width 768): 100 to 105 TFLOP/s against 22 to 45 with the vector-ALU kernel it replaces (dW of
+// Measured (4096 tokens of width 768): 105 to 118 TFLOP/s against 22 to 45 with the vector-ALU kernel it replaces (dW of
 // 768 x 3072: 878 -> 185 us; out-projection 446 -> 51 us), of 136 that a large library product reaches.
 constexpr int F32_TILE = 64;
 

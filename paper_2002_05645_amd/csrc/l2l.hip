@@ -1231,31 +1231,57 @@ int head_loss_t(l2l_ctx* c, const void* x_last, const int32_t* labels, void* dy_
   return L2L_OK;
 }
 
+// Grid of embed_bwd_fused_kernel.  `seqs` sequences per block: many, so that few blocks add into the same dPpos row and leave
+// a row of gain and bias sums, as long as 1024 blocks (four per compute unit) remain; fewer than 16 where those would leave
+// compute units idle, but no more than 16 groups for it (each adds into dPpos with an atomic: at 128 sequences of 8 tokens
+// 32 groups made its fp32 error 1.28e-7, 16 LDS additions and 8 atomics of the two-kernel form 1.12e-7).  `wide`: a wave per
+// position, where there are fewer sequences than waves and enough positions (1024 columns, one sequence: 18 against 20 us at
+// 512 tokens, 22 against 27 at 1024; at 64 tokens, two sequences, 18 against 16).  `sb` blocks share the positions of a group of sequences: a step
+// each, fewer beyond 1024 blocks.
+constexpr int EMB_FUSED_MAX = 2048;   // columns: the registers of one wave hold four groups of 512 (2048 columns: see the kernel)
+struct EmbedBwdGrid {
+  int seqs;
+  bool wide;
+  long long sb, groups;
+  long long blocks() const { return sb * groups; }
+};
+EmbedBwdGrid embed_bwd_grid(long long rows, long long S) {
+  const long long nseq = rows / S;
+  const auto groups = [&](int seqs) { return (nseq + seqs - 1) / seqs; };
+  EmbedBwdGrid g;
+  g.seqs = 16;
+  while (g.seqs < 64 && S * groups(2 * g.seqs) >= 1024) g.seqs *= 2;
+  while (g.seqs > 4 && S * groups(g.seqs) < 256 && groups(g.seqs / 2) <= 16) g.seqs /= 2;
+  g.groups = groups(g.seqs);
+  g.wide = nseq < 4 && S >= 512;
+  const long long steps = g.wide ? (S + 3) / 4 : S, per_block = (steps * g.groups + 1023) / 1024;
+  g.sb = (steps + per_block - 1) / per_block;
+  return g;
+}
+long long embed_bwd_pitch(long long H) { return up(H, ALIGN); }   // the distance of the two vectors in the packed block
+
 template <typename T>
 int embed_bwd_t(l2l_ctx* c, const int32_t* tokens, const void* dy) {
   const long long rows = c->T * c->cfg.num_ubatches;
   const T* E = (const T*)c->emb;
   const long long* eo = c->lay.eoff;
   const int H = c->cfg.hidden, S = c->cfg.seq;
-  if (H <= 2048) {   // (the registers of one wave hold four groups of 512 columns)
-    // sequences per block: many, so that few blocks add into the same dgamma and dbeta, as long as 1024 blocks (four per
-    // compute unit) remain; fewer than 16 where those would leave compute units idle
-    const long long nseq = rows / S;
-    int seqs = 16;
-    while (seqs < 64 && S * ((nseq + 2 * seqs - 1) / (2 * seqs)) >= 1024) seqs *= 2;
-    while (seqs > 4 && S * ((nseq + seqs - 1) / seqs) < 256) seqs /= 2;
-    const int nch = (H + 511) / 512;
-    return timed(c, L2L_PROF_ROWWISE, 0, 2.0 * rows * H * sizeof(T), [&] {
+  if (H <= EMB_FUSED_MAX) {
+    const EmbedBwdGrid g = embed_bwd_grid(rows, S);
+    const int nch = (H + 511) / 512, pitch = (int)embed_bwd_pitch(H);
+    float* part = c->logits;   // (the head is done with them: same stream)
+    L2L_TRY(timed(c, L2L_PROF_ROWWISE, 0, 2.0 * rows * H * sizeof(T), [&] {
       const auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)(S * ((nseq + seqs - 1) / seqs))), dim3(256), (size_t)4 * nch * 512 * sizeof(float), c->cs, tokens,
-                           E + eo[E_E], E + eo[E_P], E + eo[E_GE], (const T*)dy, c->emean, c->erstd, c->egacc + eo[E_E], c->egacc + eo[E_P],
-                           c->egacc + eo[E_GE], c->egacc + eo[E_BE], (int)rows, S, H, c->cfg.vocab, seqs);
+        hipLaunchKernelGGL(kern, dim3((unsigned)g.blocks()), dim3(256), (size_t)4 * nch * 512 * sizeof(float), c->cs, tokens, E + eo[E_E],
+                           E + eo[E_P], E + eo[E_GE], (const T*)dy, c->emean, c->erstd, c->egacc + eo[E_E], c->egacc + eo[E_P], part, pitch,
+                           (int)rows, S, H, c->cfg.vocab, g.seqs, (int)g.sb, g.wide);
       };
       if (nch == 1) go(embed_bwd_fused_kernel<T, 1>);
       else if (nch == 2) go(embed_bwd_fused_kernel<T, 2>);
       else if (nch == 3) go(embed_bwd_fused_kernel<T, 3>);
       else go(embed_bwd_fused_kernel<T, 4>);
-    });
+    }));
+    return bias_grad<float>(c, part, pitch + H, c->egacc + eo[E_GE], g.blocks(), pitch + H);   // (the bias's gradient follows at `pitch`)
   }
   L2L_TRY(timed(c, L2L_PROF_ROWWISE, 0, 0, [&] {
     const unsigned nseq = (unsigned)(rows / S);
@@ -1453,7 +1479,9 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
     L2L_TRY(dev_alloc(c, (void**)&c->chunk_cnt, ((UT + c->head_rows - 1) / c->head_rows) * 4));
     L2L_TRY(dev_alloc(c, &c->xl, c->head_rows * H * es));
     L2L_TRY(dev_alloc(c, &c->dxl, c->head_rows * H * es));
-    L2L_TRY(dev_alloc(c, (void**)&c->logits, c->head_rows * c->Vp * 4));
+    // (the logits' buffer also takes the gain and bias sums of the embedding backward's blocks)
+    const long long emb_part = H <= EMB_FUSED_MAX ? embed_bwd_grid(UT, S).blocks() * (embed_bwd_pitch(H) + H) : 0;
+    L2L_TRY(dev_alloc(c, (void**)&c->logits, std::max(c->head_rows * c->Vp, emb_part) * 4));
     L2L_TRY(dev_alloc(c, &c->dz, c->head_rows * c->Vp * es));
     HIP_TRY(c, hipEventCreateWithFlags(&c->emb_staged_ev, hipEventDisableTiming));
     HIP_TRY(c, hipEventCreateWithFlags(&c->emb_released_ev, hipEventDisableTiming));

@@ -407,124 +407,152 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(const int32_t* tokens, c
 // The same for rows of up to 2048 columns, with the gradients of LN_e's gain and bias in the same pass.  A lane keeps columns
 // lane * 8 + 512 k, k < NCH, of the row, of the position's embedding and of the three column sums (dPpos[s], dgamma, dbeta)
 // in registers; the next row's token embedding and upstream gradient are requested before the current row is worked on, and
-// the tokens and statistics of all of a wave's rows before the first.  Bound by the fp32 atomics into dE; what is gone is
-// the second and third pass over the rows, the LDS atomics per element and a column-sum kernel that read them all again.
-// 32768 rows of 1024 columns: 250 us (two kernels) -> 136 us.
-// Dynamic LDS: a row of NCH * 512 floats per wave.  seqs: sequences per block, at most 256.
+// the tokens and statistics of all of a wave's rows of a position before the first.  Bound by the fp32 atomics into dE; what
+// is gone is the second and third pass over the rows, the LDS atomics per element and a column-sum kernel that read them all.
+// The gain and bias sums leave as one row of `part` per block ([blocks][pitch + n]: dgamma, zeros up to `pitch`, dbeta),
+// which the column-sum kernel adds up: added into [n] with an atomic per block they were a chain of up to 2048 roundings
+// (fp32 error 7.6e-7 at 2048 positions of one sequence, 2.2e-7 in the two-kernel form) and queued up at L2.
+// bf16, 128 sequences of 128 tokens, two-kernel form -> an atomic per block -> this: 141 -> 90 -> 76 us at 1024 columns,
+// 243 -> 151 -> 136 at 2048 (one wave per SIMD there: 256 + 67 registers); one sequence of 1024 tokens at 1024 columns
+// 24 -> 44 -> 21 us.
+// Dynamic LDS: a row of NCH * 512 floats per wave.  seqs: sequences per block, at most 64.  A block takes positions
+// blockIdx.x % sb, that + sb, ... of its sequences, its waves every fourth row; with fewer sequences than waves (wide) four
+// positions at a time, one per wave.
 template <typename T, int NCH>
 __global__ __launch_bounds__(256) void embed_bwd_fused_kernel(const int32_t* tokens, const T* E, const T* pos, const T* gamma,
                                                               const T* dy, const float* mean, const float* rstd, float* dE,
-                                                              float* dpos, float* dgamma, float* dbeta, int rows, int S, int n,
-                                                              int V, int seqs) {
+                                                              float* dpos, float* part, int pitch, int rows, int S, int n,
+                                                              int V, int seqs, int sb, bool wide) {
   extern __shared__ __attribute__((aligned(16))) float eb_lds[];
   constexpr int NC = NCH * 512;
   constexpr bool AHEAD = sizeof(T) == 2;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int s = blockIdx.x % S, nseq = rows / S;
-  const int q0 = (blockIdx.x / S) * seqs, q1 = min(nseq, q0 + seqs);
-  int st_tok = 0;                   // lane i: token and statistics of this wave's i-th row
-  float st_mu = 0.f, st_rs = 0.f;
-  if (q0 + w + 4 * lane < q1) {
-    const int r = (q0 + w + 4 * lane) * S + s;
-    st_tok = min(max(tokens[r], 0), V - 1);   // (clamped as in the forward kernel, which reports it)
-    st_mu = mean[r];
-    st_rs = rstd[r];
-  }
-  float gam[NCH][8], ps[NCH][8], sg[NCH][8], sb[NCH][8], sp[NCH][8];
+  const int nseq = rows / S;
+  const int q0 = (blockIdx.x / sb) * seqs, q1 = min(nseq, q0 + seqs);
+  const int pw = wide ? 4 : 1;                                        // positions per step
+  const int qw = wide ? q0 : q0 + w, qstep = wide ? 1 : 4;            // this wave's rows: sequences qw, qw + qstep, ... below q1
+  float gam[NCH][8], ps[NCH][8], sg[NCH][8], sbeta[NCH][8], sp[NCH][8];
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
     const int j = lane * 8 + k * 512;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) gam[k][i] = ps[k][i] = sg[k][i] = sb[k][i] = sp[k][i] = 0.f;
-    if (j < n) {
-      load8(gamma + j, gam[k]);
-      load8(pos + (long long)s * n + j, ps[k]);
-    }
+    for (int i = 0; i < 8; ++i) gam[k][i] = sg[k][i] = sbeta[k][i] = 0.f;
+    if (j < n) load8(gamma + j, gam[k]);
   }
-  u32x4 er[NCH], dr[NCH];
-  const auto request = [&](int it) {   // the wave's it-th row, as packed 16-byte words
-    const int q = q0 + w + 4 * it;
-    if (q >= q1) return;
-    const T* e = E + (long long)__shfl(st_tok, it, 64) * n;
-    const T* d = dy + ((long long)q * S + s) * n;
-#pragma unroll
-    for (int k = 0; k < NCH; ++k) {
-      const int j = lane * 8 + k * 512;
-      if (j < n) {
-        er[k] = *(const u32x4*)(e + j);
-        dr[k] = *(const u32x4*)(d + j);
-      }
-    }
-  };
-  if constexpr (AHEAD) request(0);
   float* tw = eb_lds + w * NC;
-  for (int it = 0; q0 + w + 4 * it < q1; ++it) {
-    const long long tok = __shfl(st_tok, it, 64);
-    const float mu = __shfl(st_mu, it, 64), rs = __shfl(st_rs, it, 64);
-    float x[NCH][8], d[NCH][8];
-#pragma unroll
-    for (int k = 0; k < NCH; ++k) {
-      const int j = lane * 8 + k * 512;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) x[k][i] = d[k][i] = 0.f;
-      if (j < n) {
-        if constexpr (AHEAD) {
-          unpack8<T>(er[k], x[k]);
-          unpack8<T>(dr[k], d[k]);
-        } else {
-          load8(E + tok * n + j, x[k]);
-          load8(dy + ((long long)(q0 + w + 4 * it) * S + s) * n + j, d[k]);
-        }
-      }
-    }
-    if constexpr (AHEAD) request(it + 1);
-    float c1 = 0.f, c2 = 0.f;
-#pragma unroll
-    for (int k = 0; k < NCH; ++k) {   // (columns past n: d and gamma are zero)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        x[k][i] = (x[k][i] + ps[k][i] - mu) * rs;
-        const float gg = d[k][i] * gam[k][i];
-        c1 += gg;
-        c2 += gg * x[k][i];
-      }
-    }
-    c1 = wave_sum(c1) / n;
-    c2 = wave_sum(c2) / n;
-#pragma unroll
-    for (int k = 0; k < NCH; ++k) {
-      const int j = lane * 8 + k * 512;
-      float v[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        v[i] = rs * (d[k][i] * gam[k][i] - c1 - x[k][i] * c2);
-        sg[k][i] += d[k][i] * x[k][i];
-        sb[k][i] += d[k][i];
-        sp[k][i] += v[i];
-      }
-      *(f32x4*)(tw + j) = f32x4{v[0], v[1], v[2], v[3]};
-      *(f32x4*)(tw + j + 4) = f32x4{v[4], v[5], v[6], v[7]};
-    }
-    // the row turns through LDS so that an instruction's atomics cover whole cache lines
-    __builtin_amdgcn_wave_barrier();
-    float* de = dE + tok * n;
-    for (int col = lane; col < n; col += WAVE) atomicAdd(de + col, tw[col]);
-    __builtin_amdgcn_wave_barrier();
-  }
-  const auto fold = [&](const float (&v)[NCH][8], float* out) {   // the four waves' sums, one atomic per column
+  const auto park = [&](const float (&v)[NCH][8]) {   // in this wave's row of LDS
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
       float* p = tw + k * 512 + lane * 8;
       *(f32x4*)p = f32x4{v[k][0], v[k][1], v[k][2], v[k][3]};
       *(f32x4*)(p + 4) = f32x4{v[k][4], v[k][5], v[k][6], v[k][7]};
     }
+  };
+  const auto fold = [&](const float (&v)[NCH][8], auto&& put) {   // put(column, the four waves' sum)
+    park(v);
     __syncthreads();
-    for (int j = threadIdx.x; j < n; j += 256) atomicAdd(out + j, eb_lds[j] + eb_lds[NC + j] + eb_lds[2 * NC + j] + eb_lds[3 * NC + j]);
+    for (int j = threadIdx.x; j < n; j += 256) put(j, eb_lds[j] + eb_lds[NC + j] + eb_lds[2 * NC + j] + eb_lds[3 * NC + j]);
     __syncthreads();
   };
-  fold(sp, dpos + (long long)s * n);
-  fold(sg, dgamma);
-  fold(sb, dbeta);
+  for (int s = blockIdx.x % sb * pw + (wide ? w : 0); s < S; s += sb * pw) {
+    int st_tok = 0;                   // lane i: token and statistics of this wave's i-th row
+    float st_mu = 0.f, st_rs = 0.f;
+    if (qw + qstep * lane < q1) {
+      const int r = (qw + qstep * lane) * S + s;
+      st_tok = min(max(tokens[r], 0), V - 1);   // (clamped as in the forward kernel, which reports it)
+      st_mu = mean[r];
+      st_rs = rstd[r];
+    }
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) {
+      const int j = lane * 8 + k * 512;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ps[k][i] = sp[k][i] = 0.f;
+      if (j < n) load8(pos + (long long)s * n + j, ps[k]);
+    }
+    u32x4 er[NCH], dr[NCH];
+    const auto request = [&](int it) {   // the wave's it-th row, as packed 16-byte words
+      const int q = qw + qstep * it;
+      if (q >= q1) return;
+      const T* e = E + (long long)__shfl(st_tok, it, 64) * n;
+      const T* d = dy + ((long long)q * S + s) * n;
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) {
+        const int j = lane * 8 + k * 512;
+        if (j < n) {
+          er[k] = *(const u32x4*)(e + j);
+          dr[k] = *(const u32x4*)(d + j);
+        }
+      }
+    };
+    if constexpr (AHEAD) request(0);
+    for (int it = 0; qw + qstep * it < q1; ++it) {
+      const long long tok = __shfl(st_tok, it, 64);
+      const float mu = __shfl(st_mu, it, 64), rs = __shfl(st_rs, it, 64);
+      float x[NCH][8], d[NCH][8];
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) {
+        const int j = lane * 8 + k * 512;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[k][i] = d[k][i] = 0.f;
+        if (j < n) {
+          if constexpr (AHEAD) {
+            unpack8<T>(er[k], x[k]);
+            unpack8<T>(dr[k], d[k]);
+          } else {
+            load8(E + tok * n + j, x[k]);
+            load8(dy + ((long long)(qw + qstep * it) * S + s) * n + j, d[k]);
+          }
+        }
+      }
+      if constexpr (AHEAD) request(it + 1);
+      float c1 = 0.f, c2 = 0.f;
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) {   // (columns past n: d and gamma are zero)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          x[k][i] = (x[k][i] + ps[k][i] - mu) * rs;
+          const float gg = d[k][i] * gam[k][i];
+          c1 += gg;
+          c2 += gg * x[k][i];
+        }
+      }
+      c1 = wave_sum(c1) / n;
+      c2 = wave_sum(c2) / n;
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) {
+        const int j = lane * 8 + k * 512;
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          v[i] = rs * (d[k][i] * gam[k][i] - c1 - x[k][i] * c2);
+          sg[k][i] += d[k][i] * x[k][i];
+          sbeta[k][i] += d[k][i];
+          sp[k][i] += v[i];
+        }
+        *(f32x4*)(tw + j) = f32x4{v[0], v[1], v[2], v[3]};
+        *(f32x4*)(tw + j + 4) = f32x4{v[4], v[5], v[6], v[7]};
+      }
+      // the row turns through LDS so that an instruction's atomics cover whole cache lines
+      __builtin_amdgcn_wave_barrier();
+      float* de = dE + tok * n;
+      for (int col = lane; col < n; col += WAVE) atomicAdd(de + col, tw[col]);
+      __builtin_amdgcn_wave_barrier();
+    }
+    float* dp = dpos + (long long)s * n;
+    if (wide) {
+      park(sp);
+      __builtin_amdgcn_wave_barrier();
+      for (int col = lane; col < n; col += WAVE) atomicAdd(dp + col, tw[col]);
+      __builtin_amdgcn_wave_barrier();
+    } else {
+      fold(sp, [&](int j, float v) { atomicAdd(dp + j, v); });
+    }
+  }
+  float* row = part + (long long)blockIdx.x * (pitch + n);
+  fold(sg, [&](int j, float v) { row[j] = v; });
+  fold(sbeta, [&](int j, float v) { row[pitch + j] = v; });
+  for (int j = n + threadIdx.x; j < pitch; j += 256) row[j] = 0.f;
 }
 
 // ---- column reductions -----------------------------------------------------------------------------

@@ -1216,3 +1216,15 @@ def test_gemm_three_stage_tiles_k_tile_counts(ctx, variant, K):
     assert _gemm_case(ctx, "fp16", impl, 0, 0, 264, 392, K, out_f32=True, pad=8) < 2e-6
     if variant == 8:
         assert _gemm_case(ctx, "bf16", impl, 1, 1, 5200, 2600, K, resid=True, pad=8) < OUT16["bf16"]
+
+
+@pytest.mark.parametrize("hidden,seqs,seq", [(64, 1, 2048), (136, 3, 520), (512, 5, 1200), (1544, 2, 1032), (768, 40, 128)])
+def test_embedding_backward_gain_and_bias_sums(hidden, seqs, seq):
+    # The gradients of the embedding LayerNorm's gain and bias in fp32: a block's sums leave as a row of partial sums that
+    # the column-sum kernel adds up, whatever the number of blocks (1 to 4 positions per block, a wave per position, blocks
+    # in two rounds).  Chains of at most 64 additions of random sign, each rounding a partial sum of relative size
+    # sqrt(i / n): rms 2^-24 sqrt(64 / 2) / sqrt(3) = 1.9e-7, and as much again for the normalised values that enter.  With
+    # an atomic per block, which this replaces, (64, 1, 2048) came to 7.5e-7.
+    errs = _head_case(500, hidden, seqs, seq, "fp32", 0.1, hidden + seqs)
+    assert errs["dge"] <= 4e-7 and errs["dbe"] <= 4e-7, errs
+    assert all(e <= HEAD_TOL["fp32"] for e in errs.values()), errs

@@ -100,7 +100,7 @@ int    l2l_config_check(const l2l_config*);
    Allocates slots, accumulators and workspace on the current device.
    Tuning and test switches are taken from the environment here, once, and from nowhere else:
      L2L_NO_FUSED_ATTENTION=1  attention as batched GEMMs + softmax kernels with the score matrices in memory
-     L2L_HEAD_ROWS=n           labelled rows per pass of the LM head (default min(U T, 16384), or 8192 where its GEMMs cannot take that many)
+     L2L_HEAD_ROWS=n           labelled rows per pass of the LM head (default min(U T, 8192))
      L2L_SPLIT_WS_MB=n         room for the partial results of K-split GEMMs (default: what the layer's dW GEMMs need)
      L2L_SPLIT_ATOMICS=1       K-split GEMMs add their partial results with fp32 atomics instead
      L2L_FORCE_SPLITS=n        split factor of the accumulating fp32 GEMMs (default: by shape)

@@ -1466,13 +1466,11 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
     L2L_TRY(dev_alloc(c, (void**)&c->lab_idx, UT * 4));
     L2L_TRY(dev_alloc(c, (void**)&c->lab_cnt, (cfg->num_ubatches + 1) * 4));
     c->lab_total = c->lab_cnt + cfg->num_ubatches;
-    // Labelled rows per pass of the head.  A pass that finds no rows still costs its eight launches (42 us), and at the usual
-    // share of labels all but the first are empty: 16384 rows where dX can take its splits from the live rows and the
-    // K-strided operand of dE stays below 2 GiB (1.5 GB more of logits and their gradient at 30522 columns; at 32768
-    // tokens three of four passes were empty, 125 us of 1.8 ms, now one of two), else 8192.
-    const long long most = std::min<long long>(UT, 16384);
-    const bool wide = is16(cfg->dtype) && head_dx_live_shape_ok(c, head_dx_args(c, (int)most)) && (most + 192) * c->Vp * 2 < (1LL << 31);
-    c->head_rows = wide ? most : std::min<long long>(UT, 8192);
+    // Labelled rows per pass of the head: the logits and their gradient are the context's largest buffers (6 bytes per row and
+    // column in the 16-bit formats, 1.5 GB at 30522 columns), so a mini-batch of any size gets by with 8192 rows.  A pass
+    // that finds no rows still costs its eight launches, 16 us: 16384 rows would save two of those in 1.5 ms at 32768 tokens
+    // with 15 % of labels, and 2 % where every token has one, for twice the memory.
+    c->head_rows = std::min<long long>(UT, 8192);
     if (const char* e = getenv("L2L_HEAD_ROWS"))   // smaller passes, for tests of the multi-pass path
       if (atoll(e) > 0) c->head_rows = std::min<long long>(UT, atoll(e));
     L2L_TRY(dev_alloc(c, (void**)&c->lab_gidx, UT * 4));

@@ -1228,3 +1228,16 @@ def test_embedding_backward_gain_and_bias_sums(hidden, seqs, seq):
     errs = _head_case(500, hidden, seqs, seq, "fp32", 0.1, hidden + seqs)
     assert errs["dge"] <= 4e-7 and errs["dbe"] <= 4e-7, errs
     assert all(e <= HEAD_TOL["fp32"] for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_context_memory_of_the_head_stays_within_8192_rows(dtype):
+    # the logits and their gradient have room for 8192 labelled rows, whatever the mini-batch: beyond that a context grows by
+    # what it keeps per token (statistics, label lists, 4 bytes each), not by vocabulary times tokens
+    sizes = {}
+    for U in (2, 3, 8):      # 8192, 12288 and 32768 tokens
+        c = P.Context(P.make_config(256, 2, 512, 128, 32, U, dtype, 1e-12, 1000, 1))
+        sizes[U] = c.device_bytes()
+        c.close()
+    for U in (3, 8):
+        assert sizes[U] - sizes[2] <= (U - 2) * 4096 * 4 * 8, sizes

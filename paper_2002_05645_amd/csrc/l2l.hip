@@ -474,6 +474,9 @@ int variant_for_layout(int v, const GemmArgs& g) {
 struct TileCost { int v; double busy, lone_few, lone_all, rest; int together; };
 constexpr TileCost kCostKC[] = {{5, 0.225, 0.30, 0.47, 1.5, 4}, {7, 0.60, 0.66, 0.74, 3.0, 2}, {4, 0.69, 0.46, 0.60, 3.0, 1}, {8, 0.88, 0.57, 0.88, 4.5, 1},
                                 {6, 1.58, 1.05, 1.58, 5.8, 1}};
+// ... where the launch accumulates in fp32 (l2l_op_gemm only; the layer's dW operands are K-strided): 256 workgroups of 256 x 128
+// over 8 K splits take 1.3 us per k-tile at 1024 x 1024 x 32768 (98 us; 256 x 256 over 16 splits 83)
+constexpr TileCost kCostKCAccum[] = {kCostKC[0], kCostKC[1], kCostKC[2], {8, 0.88, 0.57, 1.20, 4.5, 1}, {6, 1.58, 1.05, 1.45, 5.8, 1}};
 // both operands K-strided (dW)
 constexpr TileCost kCostKS[] = {{7, 0.66, 0.92, 1.12, 6.0, 2}, {8, 1.42, 1.14, 1.42, 7.0, 1}, {6, 2.20, 1.70, 2.20, 10.0, 1}};
 
@@ -481,7 +484,7 @@ void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant,
   if (g.a_kc != g.b_kc || g.nbatch != 1 || g.m_dev || g.k_dev) return pick_tile(g, out_f32, variant, splits);
   const bool colsum = (g.epi & EPI_COLSUM) != 0, accum = out_f32 && g.epi == EPI_ACCUM;
   const bool can_split = split_epilogue_ok(g);
-  const TileCost* cost = g.a_kc ? kCostKC : kCostKS;
+  const TileCost* cost = !g.a_kc ? kCostKS : accum ? kCostKCAccum : kCostKC;
   const int ncost = g.a_kc ? 5 : 3;
   const int nk = std::max(1, (g.K + 63) / 64);
   double best = 1e300;

@@ -961,6 +961,7 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* part, int s
     const long long e = i * 4, r = e / n;
     const int col = (int)(e - r * n);
     f32x4 s = *(const f32x4*)(part + e);
+#pragma unroll 8   // (eight loads in flight: few rows of many slices are bound by the latency of one after the other)
     for (int k = 1; k < splits; ++k) s += *(const f32x4*)(part + k * slice + e);
     f32x4* o = (f32x4*)(out + r * ldo + col);
     *o = fresh ? s : *o + s;

@@ -479,11 +479,15 @@ constexpr TileCost kCostKC[] = {{5, 0.225, 0.30, 0.47, 1.5, 4}, {7, 0.60, 0.66, 
 constexpr TileCost kCostKCAccum[] = {kCostKC[0], kCostKC[1], kCostKC[2], {8, 0.88, 0.57, 1.20, 4.5, 1}, {6, 1.58, 1.05, 1.45, 5.8, 1}};
 // both operands K-strided (dW)
 constexpr TileCost kCostKS[] = {{7, 0.66, 0.92, 1.12, 6.0, 2}, {8, 1.42, 1.14, 1.42, 7.0, 1}, {6, 2.20, 1.70, 2.20, 10.0, 1}};
+constexpr size_t kSplitRoomMost = (size_t)16 << 20;   // floats: the most that a 16-bit context holds for its layer's shapes
 
-void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant, int* splits) {
-  if (g.a_kc != g.b_kc || g.nbatch != 1 || g.m_dev || g.k_dev) return pick_tile(g, out_f32, variant, splits);
-  const bool colsum = (g.epi & EPI_COLSUM) != 0, accum = out_f32 && g.epi == EPI_ACCUM;
-  const bool can_split = split_epilogue_ok(g);
+// whether an accumulating launch's splits may go through a workspace and split_sum_kernel
+bool split_sum_ok(const GemmArgs& g) { return g.nbatch == 1 && g.N % 8 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0; }
+
+// the rule above over the splits that fit ws_elems, beyond them (`atomics`) over splits that add into C with atomics, which
+// take 4 us per million elements (1024 x 1024 x 32768 over 16 splits: 125 us against 95 through the workspace)
+void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool atomics, int* variant, int* splits) {
+  const bool colsum = (g.epi & EPI_COLSUM) != 0, can_ws = accum ? split_sum_ok(g) : split_epilogue_ok(g);
   const TileCost* cost = !g.a_kc ? kCostKS : accum ? kCostKCAccum : kCostKC;
   const int ncost = g.a_kc ? 5 : 3;
   const int nk = std::max(1, (g.K + 63) / 64);
@@ -492,17 +496,30 @@ void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant,
     const TileCost& t = cost[i];
     if (colsum && t.v == 5) continue;   // (partial sums come per 64 rows or more)
     const long long tiles = (long long)((g.M + kTiles[t.v].bm - 1) / kTiles[t.v].bm) * ((g.N + kTiles[t.v].bn - 1) / kTiles[t.v].bn);
-    for (int s = 1; s <= (can_split ? std::min(64, std::max(1, nk / 2)) : 1); ++s) {
-      if (s > 1 && ((size_t)s * g.M * g.N > ws_elems || tiles * s > 512 * t.together)) break;
+    for (int s = 1; s <= std::min(64, std::max(1, nk / 2)); ++s) {
+      const bool in_ws = can_ws && (size_t)s * g.M * g.N <= ws_elems;
+      if (s > 1 && ((!in_ws && !atomics) || tiles * s > 512 * t.together)) break;
       const int kt = (nk + s - 1) / s;
       if (s > 1 && (nk + kt - 1) / kt != s) continue;   // an empty split
       const double wgs = (double)tiles * s, per_cu = std::ceil(wgs / 256.0), rounds = std::ceil(per_cu / t.together);
       const double lone = t.lone_few + (t.lone_all - t.lone_few) * std::min(1.0, wgs / 256.0);
       double us = kt * std::max(rounds * lone, per_cu > 1 ? per_cu * t.busy : 0.0) + rounds * t.rest;
-      if (s > 1) us += (accum ? 4.0 : 6.0) + (double)s * g.M * g.N * 8.0 / 4.0e6;
+      if (s > 1) us += in_ws ? (accum ? 4.0 : 6.0) + (double)s * g.M * g.N * 8.0 / 4.0e6 : (double)s * g.M * g.N * 4.0e-6;
       if (us < best) { best = us; *variant = t.v; *splits = s; }
     }
   }
+}
+
+void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant, int* splits) {
+  if (g.a_kc != g.b_kc || g.nbatch != 1 || g.m_dev || g.k_dev) return pick_tile(g, out_f32, variant, splits);
+  if (!(out_f32 && g.epi == EPI_ACCUM)) return choose_tile_within(g, false, ws_elems, false, variant, splits);
+  // An accumulating launch splits through the workspace wherever its best split fits (the layer's do: the sums then have a
+  // fixed order), else any way it can: a small context holds next to nothing, and a row pitch may not allow 16-byte access.
+  if (split_sum_ok(g)) {
+    choose_tile_within(g, true, std::max(ws_elems, kSplitRoomMost), false, variant, splits);
+    if (*splits == 1 || (size_t)*splits * g.M * g.N <= ws_elems) return;
+  }
+  choose_tile_within(g, true, ws_elems, true, variant, splits);
 }
 
 // whether gemm() will run this launch on the direct-to-LDS kernel, the one that honours EPI_COLSUM; otherwise the
@@ -528,7 +545,7 @@ int launch_split_through_workspace(int v, const GemmArgs& g, hipStream_t s, int 
   const long long slice = (long long)g.M * g.N;
   const bool accum = out_f32 && g.epi == EPI_ACCUM;
   if (!(splits > 1 && kTiles[v].direct && g.nbatch == 1 && ws && !g.m_dev && !g.k_dev &&
-        (accum ? g.N % 8 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0 : split_epilogue_ok(g))))
+        (accum ? split_sum_ok(g) : split_epilogue_ok(g))))
     return SPLIT_NOT_APPLICABLE;
   const int nk = (g.K + kTiles[v].bk - 1) / kTiles[v].bk, per = (nk + splits - 1) / splits;
   splits = (nk + per - 1) / per;   // no empty split: every slice of the workspace gets written
@@ -1492,7 +1509,7 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
   }
   {   // workspace of the K-split GEMMs: the largest room that the layer's shapes ask for, within 64 MB (fp32: 32 MB)
     const bool f32 = !is16(cfg->dtype);
-    const size_t most = (size_t)(f32 ? 8 : 16) << 20;
+    const size_t most = f32 ? (size_t)8 << 20 : kSplitRoomMost;
     size_t need = 0;
     const int h = cfg->hidden, f = cfg->ffn, m = (int)Mg;
     const int shapes[][3] = {{m, 3 * h, h}, {m, h, h}, {m, f, h}, {m, h, f}, {m, h, 3 * h}, {h, 3 * h, m}, {h, h, m}, {h, f, m}, {f, h, m}};

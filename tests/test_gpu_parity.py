@@ -1241,3 +1241,24 @@ def test_context_memory_of_the_head_stays_within_8192_rows(dtype):
         c.close()
     for U in (3, 8):
         assert sizes[U] - sizes[2] <= (U - 2) * 4096 * 4 * 8, sizes
+
+
+@pytest.mark.parametrize("kc", [0, 1])
+@pytest.mark.parametrize("M,N,K,pad", [(256, 256, 32768, 8), (256, 256, 32768, 3), (64, 64, 65536, 8), (1024, 1024, 16384, 8)])
+def test_gemm_accumulate_splits_without_room_in_the_workspace(ctx, M, N, K, pad, kc):
+    # An accumulating GEMM with few tiles is split over K whatever the context holds: its workspace may be next to nothing
+    # (this one's) and the rows of C may not be 16-byte aligned; the splits then add with atomics.  Shown by rounding: the
+    # first product is 2^30, where one unit in the last place is 128, so a single chain swallows the ones that follow it,
+    # 16 at a time; the sums of the other splits are exact.
+    A = torch.ones((M, K) if kc else (K, M), dtype=torch.bfloat16, device="cuda")
+    Bm = torch.ones((N, K) if kc else (K, N), dtype=torch.bfloat16, device="cuda")
+    for t in (A, Bm):
+        (t[:, 0] if kc else t[0]).fill_(2.0 ** 15)
+    C = torch.zeros((M, N + pad), device="cuda")
+    ctx.op_gemm(P.L2L_BF16, True, kc, kc, M, N, K, A, K if kc else M, Bm, K if kc else N, C, N + pad, accumulate=True)
+    torch.cuda.synchronize()
+    over = C[:, :N].double() - 2.0 ** 30
+    assert not C[:, N:].any()
+    assert float(over.min()) >= K / 2 - 128 and float(over.max()) <= K, (float(over.min()), float(over.max()))
+    for dtype in ("bf16", "fp16"):
+        assert _gemm_case(ctx, dtype, 0, kc, kc, 200, 264, 4096, accumulate=True, out_f32=True, pad=pad) < 2e-6

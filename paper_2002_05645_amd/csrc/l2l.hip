@@ -479,7 +479,6 @@ constexpr TileCost kCostKC[] = {{5, 0.225, 0.30, 0.47, 1.5, 4}, {7, 0.60, 0.66, 
 constexpr TileCost kCostKCAccum[] = {kCostKC[0], kCostKC[1], kCostKC[2], {8, 0.88, 0.57, 1.20, 4.5, 1}, {6, 1.58, 1.05, 1.45, 5.8, 1}};
 // both operands K-strided (dW)
 constexpr TileCost kCostKS[] = {{7, 0.66, 0.92, 1.12, 6.0, 2}, {8, 1.42, 1.14, 1.42, 7.0, 1}, {6, 2.20, 1.70, 2.20, 10.0, 1}};
-constexpr size_t kSplitRoomMost = (size_t)16 << 20;   // floats: the most that a 16-bit context holds for its layer's shapes
 
 // whether an accumulating launch's splits may go through a workspace and split_sum_kernel
 bool split_sum_ok(const GemmArgs& g) { return g.nbatch == 1 && g.N % 8 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0; }
@@ -513,13 +512,14 @@ void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool ato
 void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant, int* splits) {
   if (g.a_kc != g.b_kc || g.nbatch != 1 || g.m_dev || g.k_dev) return pick_tile(g, out_f32, variant, splits);
   if (!(out_f32 && g.epi == EPI_ACCUM)) return choose_tile_within(g, false, ws_elems, false, variant, splits);
-  // An accumulating launch splits through the workspace wherever its best split fits (the layer's do: the sums then have a
-  // fixed order), else any way it can: a small context holds next to nothing, and a row pitch may not allow 16-byte access.
-  if (split_sum_ok(g)) {
-    choose_tile_within(g, true, std::max(ws_elems, kSplitRoomMost), false, variant, splits);
-    if (*splits == 1 || (size_t)*splits * g.M * g.N <= ws_elems) return;
-  }
-  choose_tile_within(g, true, ws_elems, true, variant, splits);
+  // An accumulating launch splits through the workspace where two slices fit (the layer's do, if it wants any: the sums then
+  // have a fixed order), else with atomics where the rule by size would: a small context holds next to nothing, and a row
+  // pitch may not allow 16-byte access.
+  choose_tile_within(g, true, ws_elems, false, variant, splits);
+  if (*splits > 1 || (split_sum_ok(g) && (size_t)2 * g.M * g.N <= ws_elems)) return;
+  int v, by_size;
+  pick_tile(g, true, &v, &by_size);
+  if (by_size > 1) choose_tile_within(g, true, ws_elems, true, variant, splits);
 }
 
 // whether gemm() will run this launch on the direct-to-LDS kernel, the one that honours EPI_COLSUM; otherwise the
@@ -1509,7 +1509,7 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
   }
   {   // workspace of the K-split GEMMs: the largest room that the layer's shapes ask for, within 64 MB (fp32: 32 MB)
     const bool f32 = !is16(cfg->dtype);
-    const size_t most = f32 ? (size_t)8 << 20 : kSplitRoomMost;
+    const size_t most = (size_t)(f32 ? 8 : 16) << 20;
     size_t need = 0;
     const int h = cfg->hidden, f = cfg->ffn, m = (int)Mg;
     const int shapes[][3] = {{m, 3 * h, h}, {m, h, h}, {m, f, h}, {m, h, f}, {m, h, 3 * h}, {h, 3 * h, m}, {h, h, m}, {h, f, m}, {f, h, m}};

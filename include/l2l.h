@@ -301,7 +301,8 @@ int l2l_op_gemm(l2l_ctx*, int in_dtype, int out_f32, int a_kc, int b_kc, int M, 
    L2L_EPI_ACCUM: C += result (fp32 C).
    L2L_EPI_COLSUM: also leaves partial column sums of the stored values: colsum is device fp32 [colsum_rows][N];
      *colsum_rows_used (host int, may be NULL) receives how many rows were written; their sum over rows is the column
-     sum of C (the bias gradient db1 = colsum(dU1) without a pass over dU1).  Only where the direct-to-LDS MFMA
+     sum of C (the bias gradient db1 = colsum(dU1) without a pass over dU1).  ceil(M / 64) rows suffice for any shape,
+     ceil(M / 128) where M, N and K are at least 256.  Only where the direct-to-LDS MFMA
      kernel takes the launch with 16-byte aligned rows (impl = 0, 16-bit output): otherwise L2L_E_ARG. */
 enum { L2L_EPI_GELU = 1, L2L_EPI_GELUGRAD = 2, L2L_EPI_ACCUM = 4, L2L_EPI_COLSUM = 8, L2L_EPI_KEEPGRAD = 16, L2L_EPI_MULAUX = 32 };
 int l2l_op_gemm_ex(l2l_ctx*, int in_dtype, int out_f32, int a_kc, int b_kc, int M, int N, int K,

@@ -210,6 +210,7 @@ struct GemmArgs {
   int fresh;              // EPI_ACCUM: 1 = C holds no sum yet, its content counts as zero and need not be
   float* colsum;          // EPI_COLSUM: fp32 [ceil(M / WM)][N] (WM = rows of a wave's tile): row r receives the column sums
                           // of the values stored to rows r WM .. r WM + WM - 1 of C (plain stores; the caller adds the rows up)
+  long long colsum_rows;  // rows that colsum has, 0 = ceil(M / 64) or more
 };
 
 // K splits of a launch whose rows M only the device knows, over at most `wgs` workgroups: as many as give every live tile

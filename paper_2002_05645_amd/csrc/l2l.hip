@@ -511,7 +511,12 @@ void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool ato
 
 void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant, int* splits) {
   if (g.a_kc != g.b_kc || g.nbatch != 1 || g.m_dev || g.k_dev) return pick_tile(g, out_f32, variant, splits);
-  if (!(out_f32 && g.epi == EPI_ACCUM)) return choose_tile_within(g, false, ws_elems, false, variant, splits);
+  if (!(out_f32 && g.epi == EPI_ACCUM)) {
+    choose_tile_within(g, false, ws_elems, false, variant, splits);
+    // (a caller's buffer of column sums may have room for the wider wave tiles that the rule by size takes, and no more)
+    if ((g.epi & EPI_COLSUM) && g.colsum_rows > 0 && (g.M + kTiles[*variant].wm - 1) / kTiles[*variant].wm > g.colsum_rows) pick_tile(g, out_f32, variant, splits);
+    return;
+  }
   // An accumulating launch splits through the workspace where two slices fit (the layer's do, if it wants any: the sums then
   // have a fixed order), else with atomics where the rule by size would: a small context holds next to nothing, and a row
   // pitch may not allow 16-byte access.
@@ -2134,6 +2139,7 @@ int l2l_op_gemm_ex(l2l_ctx* c, int in_dtype, int out_f32, int a_kc, int b_kc, in
   if (epi & L2L_EPI_COLSUM) {
     int rows = 0;
     g.colsum = colsum;
+    g.colsum_rows = colsum_rows;
     if (!colsum || impl != 0 || M == 0 || N == 0 || !colsum_in_gemm_ok(in_dtype, out_f32 != 0, g, &rows))
       return fail(c, L2L_E_ARG, "l2l_op_gemm: column sums are not available for this shape, layout or implementation");
     if (rows > colsum_rows) return fail(c, L2L_E_ARG, "l2l_op_gemm: column sums need %d rows, the buffer has %lld", rows, colsum_rows);

@@ -1262,3 +1262,21 @@ def test_gemm_accumulate_splits_without_room_in_the_workspace(ctx, M, N, K, pad,
     assert float(over.min()) >= K / 2 - 128 and float(over.max()) <= K, (float(over.min()), float(over.max()))
     for dtype in ("bf16", "fp16"):
         assert _gemm_case(ctx, dtype, 0, kc, kc, 200, 264, 4096, accumulate=True, out_f32=True, pad=pad) < 2e-6
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 256, 256), (1000, 1024, 264), (4096, 1024, 512)])
+def test_gemm_column_sums_into_a_row_per_128(ctx, M, N, K):
+    # from 256 rows, columns and k on, one row of partial sums per 128 rows of C has always been enough; a tile with smaller
+    # wave tiles must not be chosen where the buffer has no more than that
+    A = torch.randn(M, K, device="cuda").bfloat16()
+    Bm = torch.randn(N, K, device="cuda").bfloat16()
+    C = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
+    rows = (M + 127) // 128
+    cs = torch.full((rows + 1, N), 12345.0, device="cuda")
+    used = ctx.op_gemm_ex(P.L2L_BF16, False, 1, 1, M, N, K, A, K, Bm, K, C, N, epi=B.EPI_COLSUM, colsum=cs, colsum_rows=rows)
+    torch.cuda.synchronize()
+    ref = A.double() @ Bm.double().t()
+    assert used == rows and torch.all(cs[rows] == 12345.0)
+    tol = 2e-6 * (A.double().abs() @ Bm.double().abs().t()).sum(0) + 1e-6 * ref.abs().sum(0)      # as in _gemm_ex_case
+    assert torch.all((cs[:used].double().sum(0) - ref.sum(0)).abs() <= tol)
+    assert torch.all((C.double() - ref).abs() <= 0.5 * ULP["bf16"] * 1.001 * ref.abs() + 2e-6 * (A.double().abs() @ Bm.double().abs().t()))

@@ -599,12 +599,8 @@ int gemm(l2l_ctx* c, int dtype, bool out_f32, const GemmArgs& g, int impl = 0, i
     }
   }
   const bool fresh = g.fresh && out_f32 && g.epi == EPI_ACCUM;
-  if (g.fresh && !use_mfma) {
-    GemmArgs s = g;
-    s.fresh = 0;
-    if (fresh) s.epi = 0;
-    return gemm(c, dtype, out_f32, s, impl, cls);
-  }
+  GemmArgs gp = g;   // for the kernels without K splits that add: a first result is stored
+  if (fresh) gp.epi = 0;
   return timed(c, cls, flops, bytes, [&] {
     if (use_mfma) {
       // with a workspace for partial sums the tile and the splits are chosen by estimated time; a forced tile, forced
@@ -629,15 +625,15 @@ int gemm(l2l_ctx* c, int dtype, bool out_f32, const GemmArgs& g, int impl = 0, i
       else if (fresh) clear_matrix(c, g);
       launch_mfma_variant(v, gr, c->cs, splits, out_f32, dtype == L2L_FP16);
     } else if (dtype == L2L_BF16) {
-      if (out_f32) launch_plain<bf16, float>(g, c->cs);
-      else launch_plain<bf16, bf16>(g, c->cs);
+      if (out_f32) launch_plain<bf16, float>(gp, c->cs);
+      else launch_plain<bf16, bf16>(gp, c->cs);
     } else if (dtype == L2L_FP16) {
-      if (out_f32) launch_plain<fp16, float>(g, c->cs);
-      else launch_plain<fp16, fp16>(g, c->cs);
-    } else if (impl == 0 && f32_mfma_ok(g)) {
-      gemm_f32(g, c->cs, c->split_ws, c->split_ws_elems);
+      if (out_f32) launch_plain<fp16, float>(gp, c->cs);
+      else launch_plain<fp16, fp16>(gp, c->cs);
+    } else if (impl == 0 && f32_mfma_ok(gp)) {
+      gemm_f32(gp, c->cs, c->split_ws, c->split_ws_elems);
     } else {
-      launch_plain<float, float>(g, c->cs);
+      launch_plain<float, float>(gp, c->cs);
     }
   }, shape);
 }

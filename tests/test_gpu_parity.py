@@ -1280,3 +1280,28 @@ def test_gemm_column_sums_into_a_row_per_128(ctx, M, N, K):
     tol = 2e-6 * (A.double().abs() @ Bm.double().abs().t()).sum(0) + 1e-6 * ref.abs().sum(0)      # as in _gemm_ex_case
     assert torch.all((cs[:used].double().sum(0) - ref.sum(0)).abs() <= tol)
     assert torch.all((C.double() - ref).abs() <= 0.5 * ULP["bf16"] * 1.001 * ref.abs() + 2e-6 * (A.double().abs() @ Bm.double().abs().t()))
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_profile_gemm_table_has_the_weight_gradients_as_they_were_asked_for(dtype):
+    # the first launch group of a layer visit stores its dW over the accumulator, whichever kernel takes it: one row per
+    # shape in the table, with the accumulate flag (16 as the library numbers them), both groups in it, and no empty rows
+    H, F, seq = 136, 264, 40
+    cfg = P.make_config(H, 1, F, seq, 2, 2, dtype, 1e-12, 0, 1)
+    c = P.Context(cfg)
+    try:
+        total = P.lib().l2l_layer_packed_elems(cfg)
+        dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+        host = (torch.randn(total) * 0.05).to(dt).pin_memory()
+        c.param_stage(0, host, 0)
+        x = torch.randn(2, 2, seq, H, device="cuda").to(dt)
+        c.profile(1)
+        c.layer_bwd(0, 0, x, torch.randn_like(x))
+        rows = c.profile_gemm_table()
+        c.profile(0)
+        c.sync()
+    finally:
+        c.close()
+    assert all(r["launches"] > 0 for r in rows), rows
+    dw = {(r["M"], r["N"]): r["launches"] for r in rows if r["epi"] == 16}
+    assert dw == {(H, 3 * H): 2, (H, H): 2, (H, F): 2, (F, H): 2}, rows

@@ -596,7 +596,7 @@ def test_layer_deep_wide_full_width_bf16():
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 def test_layer_unfused_attention_path_still_matches(monkeypatch, dtype):
-    # the batched-GEMM attention path (used for other head widths / sequence lengths), forced at a fused shape
+    # the batched-GEMM attention path (used for head widths above 128 and in fp32), forced at a fused shape
     monkeypatch.setenv("L2L_NO_FUSED_ATTENTION", "1")
     w = S.Workload("unfused", 1, 128, 2, 256, 64, 50, 3, 2, dtype, 1.0, 80)
     _assert_errs(_layer_case(w), TOL[dtype])
@@ -1305,3 +1305,71 @@ def test_profile_gemm_table_has_the_weight_gradients_as_they_were_asked_for(dtyp
     assert all(r["launches"] > 0 for r in rows), rows
     dw = {(r["M"], r["N"]): r["launches"] for r in rows if r["epi"] == 16}
     assert dw == {(H, 3 * H): 2, (H, H): 2, (H, F): 2, (F, H): 2}, rows
+
+
+@pytest.mark.parametrize("switch", [None, "L2L_SPLIT_ATOMICS=1", "L2L_FORCE_SPLITS=4", "L2L_SPLIT_WS_MB=0"])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("group", [1, 3])
+def test_split_layer_gradients_do_not_depend_on_what_the_accumulator_held(monkeypatch, group, dtype, switch):
+    # as test_layer_gradients_do_not_depend_on_what_the_accumulator_held with enough tokens (16 and 48 k-tiles of 64) that
+    # the first group's dW GEMMs are split over K: into the workspace, whose sum stores, and with atomics, whose target is
+    # cleared first.  Either accumulator is used twice; the second user's upstream gradients are the first's.
+    if switch:
+        monkeypatch.setenv(*switch.split("="))
+    H, seq = 136, 128
+    cfg = P.make_config(H, 1, 264, seq, 8, 3, dtype, 1e-12, 0, group)
+    dt = {"fp16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    total = P.lib().l2l_layer_packed_elems(cfg)
+    c = P.Context(cfg)
+    host = (torch.randn(total, device="cuda", generator=gen) * 0.05).to(dt).cpu().pin_memory()
+    c.param_stage(0, host, 0)
+    x = torch.randn((3, 8, seq, H), device="cuda", generator=gen).to(dt)
+    dy0 = torch.randn(x.shape, device="cuda", generator=gen).to(dt)
+    lands = []
+    for visit in range(4):
+        land = torch.zeros(total).pin_memory()
+        c.layer_bwd(0, 0, x, dy0.clone())
+        c.grad_drain(0, land)
+        c.sync()
+        lands.append(land)
+    c.close()
+    for land in lands[1:]:      # fp32 sums in another order (atomics) at most
+        assert float((land - lands[0]).norm() / lands[0].norm()) < 1e-5
+
+
+@pytest.mark.parametrize("stats", [False, True])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("hidden,heads", [(1032, 3), (1152, 12), (1528, 1)])
+def test_layer_three_column_groups(hidden, heads, dtype, stats):
+    # LayerNorm backward with three column groups of 512 of which the last is partly filled, from R2 and (stats) from the
+    # stashed output; 120 rows a group: the last block's waves run out of rows at different times
+    w = S.Workload("groups3", 1, hidden, heads, 256, 40, 50, 3, 2, dtype, 1.0, 700 + heads)
+    _assert_errs(_layer_case(w, stats=stats, dy_scale=256.0 if dtype == "fp16" else 1.0), TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("head_rows,ws_mb,seqs,label_prob", [(256, None, 5, 1.0), (256, None, 5, 0.3), (512, None, 13, 1.0), (256, 1, 5, 1.0),
+                                                             (None, None, 80, 1.0), (None, None, 80, 0.1)])
+def test_head_in_several_passes_16_bit(monkeypatch, head_rows, ws_mb, seqs, label_prob, dtype):
+    # passes whose dX takes its K splits from the live rows, then a last one below 256 rows, which sums in fp32 and rounds
+    # afterwards (520 and 1352 tokens; 8320 at the default of 8192 rows); passes without a labelled row; no room for the
+    # live splits in the workspace
+    if head_rows:
+        monkeypatch.setenv("L2L_HEAD_ROWS", str(head_rows))
+    if ws_mb:
+        monkeypatch.setenv("L2L_SPLIT_WS_MB", str(ws_mb))
+    errs = _head_case(1000 if seqs == 80 else 5002, 264, seqs, 104, dtype, label_prob, seqs)
+    assert all(e <= HEAD_TOL[dtype] for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("K", [8, 64, 72, 136, 328])
+def test_gemm_64_by_64_tiles(ctx, K):
+    # the 64 x 64 tile is built for K-contiguous operands (another tile takes the other layouts when it is asked for): edges
+    # in both directions, one to six k-tiles, 16-byte and element-wise epilogue
+    impl = 105
+    for M, N in ((1, 8), (63, 72), (264, 392)):
+        assert _gemm_case(ctx, "bf16", impl, 1, 1, M, N, K, bias=True, resid=True, alpha=0.5, pad=8) < OUT16["bf16"]
+        assert _gemm_case(ctx, "fp16", impl, 1, 1, M, N, K, bias=True, gelu=True, pad=8) < OUT16["fp16"]
+        assert _gemm_case(ctx, "bf16", impl, 1, 1, M, N, K, out_f32=True, pad=3) < 2e-6
+        assert _gemm_case(ctx, "fp16", impl, 1, 1, M, N, K, accumulate=True, out_f32=True, pad=8) < 2e-6

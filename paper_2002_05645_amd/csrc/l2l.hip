@@ -1212,15 +1212,17 @@ int head_loss_t(l2l_ctx* c, const void* x_last, const int32_t* labels, void* dy_
     // knows, so the kernel takes the K splits from there: all compute units work whatever the share of labelled rows, and
     // one kernel adds the slices up and rounds.  (4915 of 8192 rows, H = 1024, V = 30522: 548 us with two splits fixed
     // by the rows there is room for, atomics and two more kernels; 379 + 13 us this way.)
+    bool scattered = false;   // dXl is where it belongs in dy_out
     if constexpr (sizeof(T) == 2) {
       GemmArgs h = head_dx_args(c, rows);
       h.m_dev = cnt;
       if (head_dx_live_ok(c, h)) {
+        scattered = true;
         h.C = c->split_ws;
         h.live_splits = 1;
         L2L_TRY(timed(c, L2L_PROF_OTHER, 2.0 * rows * H * (double)V, 0, [&] { launch_mfma_variant(6, h, c->cs, 1, true, dt == L2L_FP16); }));
         L2L_TRY(timed(c, L2L_PROF_OTHER, 0, 0, [&] {
-          hipLaunchKernelGGL(live_sum_kernel<T>, dim3(1024), dim3(256), 0, c->cs, c->split_ws, cnt, rows, H, V, (T*)c->dxl);
+          hipLaunchKernelGGL(live_sum_kernel<T>, dim3(1024), dim3(256), 0, c->cs, c->split_ws, cnt, rows, H, V, idx, (T*)dy_out);
         }));
       } else {
         // as an accumulating fp32 GEMM into a cleared buffer it is split over K like the dW GEMMs, and rounded afterwards
@@ -1239,10 +1241,12 @@ int head_loss_t(l2l_ctx* c, const void* x_last, const int32_t* labels, void* dy_
       h.m_dev = cnt;
       L2L_TRY(gemm(c, dt, false, h, 0, L2L_PROF_OTHER));
     }
-    L2L_TRY(timed(c, L2L_PROF_OTHER, 0, 0, [&] {
-      hipLaunchKernelGGL((rows_by_index_kernel<T, true>), dim3((rows + 3) / 4), dim3(256), 0, c->cs, (const T*)c->dxl, (T*)dy_out,
-                         idx, cnt, H);
-    }));
+    if (!scattered) {
+      L2L_TRY(timed(c, L2L_PROF_OTHER, 0, 0, [&] {
+        hipLaunchKernelGGL((rows_by_index_kernel<T, true>), dim3((rows + 3) / 4), dim3(256), 0, c->cs, (const T*)c->dxl, (T*)dy_out,
+                           idx, cnt, H);
+      }));
+    }
     // dE += dz^T Xl ; dbv += colsum(dz)
     GemmArgs w = gemm_args(V, H, rows, c->dz, Vp, 0, c->xl, H, 0, c->egacc + eo[E_E], H);
     w.epi = EPI_ACCUM; w.k_dev = cnt;

@@ -990,22 +990,22 @@ __global__ __launch_bounds__(256) void split_epilogue_kernel(const float* part, 
   }
 }
 
-// out[m, :] = sum of the slices of a live_splits GEMM (*cnt live rows of n columns, contraction over K), rounded to E;
-// n a multiple of 8, out dense.
+// out[idx[m], :] = sum of the slices of a live_splits GEMM (*cnt live rows of n columns, contraction over K), rounded to E;
+// n a multiple of 8, out dense.  (Rows go where they belong from here: a copy of them and a launch less per pass.)
 template <typename E>
-__global__ __launch_bounds__(256) void live_sum_kernel(const float* part, const int* cnt, int rows, int n, int K, E* out) {
-  const int M = min(rows, *cnt);
+__global__ __launch_bounds__(256) void live_sum_kernel(const float* part, const int* cnt, int rows, int n, int K, const int32_t* idx, E* out) {
+  const int M = min(rows, *cnt), n8 = n / 8;
   const LiveSplits ls = live_splits(M, n, K);
-  const long long total = (long long)M * n / 8;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < M * n8; i += gridDim.x * 256) {   // (M n / 8 stays far below 2^31: the tiles are at most 256)
+    const int m = i / n8;
     float v[8], t[8];
-    load8(part + 8 * i, v);
+    load8(part + 8LL * i, v);
     for (int k = 1; k < ls.splits; ++k) {
-      load8(part + k * ls.stride + 8 * i, t);
+      load8(part + k * ls.stride + 8LL * i, t);
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] += t[e];
     }
-    store8(out + 8 * i, v);
+    store8(out + (long long)idx[m] * n + (i - m * n8) * 8, v);
   }
 }
 

@@ -101,9 +101,10 @@ int    l2l_config_check(const l2l_config*);
    Tuning and test switches are taken from the environment here, once, and from nowhere else:
      L2L_NO_FUSED_ATTENTION=1  attention as batched GEMMs + softmax kernels with the score matrices in memory
      L2L_HEAD_ROWS=n           labelled rows per pass of the LM head (default min(U T, 8192))
-     L2L_SPLIT_WS_MB=n         room for the partial results of K-split GEMMs (default: what the layer's dW GEMMs need)
-     L2L_SPLIT_ATOMICS=1       K-split GEMMs add their partial results with fp32 atomics instead
-     L2L_FORCE_SPLITS=n        split factor of the accumulating fp32 GEMMs (default: by shape)
+     L2L_SPLIT_WS_MB=n         room for the partial results of K-split GEMMs (default: what the layer's GEMMs and the head's dX need,
+                               at most 64 MB, in fp32 32 MB)
+     L2L_SPLIT_ATOMICS=1       K-split GEMMs with 16-bit operands add their partial results with fp32 atomics instead
+     L2L_FORCE_SPLITS=n        split factor of the accumulating GEMMs with 16-bit operands (default: by shape)
      L2L_COPY_ROWS=0           gradient drains issued as plain copies (the runtime's copy kernel) instead of rows of 64 KiB (DMA engine)
      L2L_NO_WEIGHT_TRANSPOSE=1 forward GEMMs read the weights as stored, as a K-strided operand (no [out,in] copies per stage)
      L2L_GEMM_RESIDENT=0       one workgroup per GEMM tile instead of one resident workgroup per compute unit */

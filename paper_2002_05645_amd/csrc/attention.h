@@ -696,11 +696,14 @@ void attn_bwd_dkv_long_kernel(const E* qkv, const E* dout, const float* lse, con
 // The same three kernels as for long sequences, with the head width padded to DP = 32, 64, 96 or 128: columns d .. DP - 1
 // of every image and fragment are zeros (16-byte chunks past d are sent out of the descriptor's range), keys past S get
 // no weight, queries past S are computed on zeros and not stored.  A workgroup owns 128 queries (or keys) and walks the
-// other index in chunks of 64 rows, which keeps two images of the widest head within 32 KB and several workgroups on a
-// compute unit: nothing is prefetched, the other workgroups run under one's loads.
-// Bound by the latency of the chain load -> products -> softmax -> products at these sizes.  Measured at 35 sequences of
-// 200 tokens with 12 heads of 96, against the batched GEMM launches around softmax kernels they replace, which wrote S x S
-// matrices to memory and read them back: forward 121 -> 35 us, backward 183 -> 94 us.
+// other index in chunks of 64 rows, which keeps two images of the widest head within 32 KB.  Registers decide how many
+// workgroups share a compute unit: 4, 3, 2, 2 of the forward kernel at 32, 64, 96, 128 columns, 5, 4, 2, 2 of dQ, 4, 2, 2, 1
+// of dK / dV.  Nothing is prefetched: where there are others they run under one's loads, dK / dV at 128 columns waits.
+// Bound by the latency of the chain load -> products -> softmax -> products at these sizes.  Measured against the batched
+// GEMM launches around softmax kernels they replace, which wrote S x S matrices to memory and read them back, forward and
+// dQ with dK / dV: 35 sequences of 200 tokens, 12 heads of 96: 121 -> 35, 183 -> 94 us; 64 of 128 tokens, 48 heads of 128:
+// 269 -> 103, 439 -> 380; 16 of 512 tokens, 16 heads of 128: 263 -> 62, 412 -> 247; 32 of 200 tokens, 16 heads of 32:
+// 113 -> 20, 158 -> 49.  Nor was any slower at 8 to 4096 tokens and heads of 8 to 128.
 constexpr int CHA = 64;   // rows per chunk
 
 template <int DP>

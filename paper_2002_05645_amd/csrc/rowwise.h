@@ -749,8 +749,8 @@ __global__ __launch_bounds__(256) void ce_kernel(const float* z, long long ldz, 
 
 // The same with the row held in registers: 512 threads, NC chunks of 4 columns each (Vp <= 2048 NC), so that the logits are
 // read once, with 16-byte loads, and each exponential is taken once.  Bound by memory: one pass over z and one over dz.  Two
-// blocks fit a compute unit (64 row values per thread at NC = 16), and one's loads run under the other's reductions.  Rows
-// are dealt out over a fixed grid: the list of labelled rows is usually far shorter than what it has room for.
+// blocks and more fit a compute unit up to NC = 8 (89 registers), so that one's loads run under the other's reductions; at
+// NC = 16 one does (161; 177 in fp32), and its loads run under nothing.  Rows are dealt out over a fixed grid: the list of labelled rows is usually far shorter than what it has room for.
 // 4915 rows of 30522 columns (0.9 GB): 562 us with the loop above, which reads the row four times, 218 us here.
 constexpr int CE_NT = 512;
 template <typename T, int NC>

@@ -538,6 +538,56 @@ __device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70);
 // ... and until every LDS read this wave issued has returned (vmcnt(0) lgkmcnt(0))
 __device__ __forceinline__ void wait_vm0_lds0() { __builtin_amdgcn_s_waitcnt(0x0070); }
 
+// One pass of the direct-to-LDS kernels' 16-byte epilogue path: 8 columns of row m, v[] = alpha * acc on entry, stored to cp.
+// bias8, csum8: the lane's bias values and column sums; pre: its 16 bytes of the residual or the kept activation, requested
+// some passes earlier (pre_aux / pre_res say which).
+template <typename E, typename TC>
+__device__ __forceinline__ void epilogue_pass(const GemmArgs& g, int epi, bool pre_aux, bool pre_res, u32x4 pre, const float (&bias8)[8],
+                                              int m, int ncol, TC* cp, float (&v)[8], float (&csum8)[8]) {
+  float tt[8];
+  if (epi & EPI_BIAS) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += bias8[e];
+  }
+  if (epi & EPI_GELU) {
+    if ((epi & EPI_KEEPGRAD) && g.aux_out) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) gelu_and_grad_epi<E>(v[e], v[e], tt[e]);
+      store8((E*)g.aux_out + (long long)m * g.ldaux + ncol, tt);
+    } else {
+      if (g.aux_out) store8((E*)g.aux_out + (long long)m * g.ldaux + ncol, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = gelu_epi<E>(v[e]);
+    }
+  }
+  if (pre_aux) {
+    unpack8<E>(pre, tt);
+    if (epi & EPI_MULAUX) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] *= tt[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_epi<E>(tt[e]);
+    }
+  }
+  if (epi & EPI_RESID) {
+    if (pre_res) unpack8<E>(pre, tt);
+    else load8((const E*)g.resid + (long long)m * g.ldr + ncol, tt);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += tt[e];
+  }
+  if (epi & EPI_ACCUM) {
+    load8(cp, tt);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += tt[e];
+  }
+  store8(cp, v);
+  if (epi & EPI_COLSUM) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) csum8[e] += v[e];
+  }
+}
+
 // dynamic LDS of gemm_mfma_dlds_kernel: NST stages; the epilogue's strips (one of 32 x (WN + 4) floats per wave) sit
 // behind the first stage, which by then is receiving the next tile
 template <int BM, int BN, int WM, int WN, int NST = 2>
@@ -548,17 +598,13 @@ constexpr int dlds_lds_bytes() {
 
 // EPI >= 0: the epilogue flags are this compile-time constant (the launcher guarantees g.epi == EPI), which takes
 // the flag tests and the code of the unused operations out of the unrolled epilogue; EPI = -1: flags read from g.epi.
-// EPI = EPI_LIVE_SPLITS: fp32 partial results of a K split whose factor follows from the rows that *m_dev says are live
-// (live_splits): a grid of LIVE_WGS workgroups, of which tile count x splits have work, one tile each, no epilogue.
 // NST: LDS stages, 2 or 3.  With three a k-tile's loads are issued two k-tiles ahead, for the tiles whose k-tile is
 // shorter than the way to memory where a workgroup is alone on its compute unit (4096 x 1024 x 4096 on 128 x 128
 // tiles: 51.6 -> 41.8 us; 7000 x 1152 x 4616 on 256 x 128: 94 -> 83 us).
-constexpr int EPI_LIVE_SPLITS = -2;
 template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, typename TC, typename E = bf16, int EPI = -1, int NST = 2>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_kernel(GemmArgs g) {
   constexpr int BK = 64;
-  constexpr bool LIVE = EPI == EPI_LIVE_SPLITS;
-  const int epi = EPI >= 0 ? EPI : LIVE ? 0 : g.epi;
+  const int epi = EPI >= 0 ? EPI : g.epi;
   const float alpha = EPI >= 0 ? 1.0f : g.alpha;   // the launcher sends only alpha = 1 to the kernels with compiled-in flags
   constexpr int NWM = BM / WM, NWN = BN / WN, NT = NWM * NWN * 64;
   constexpr int FM = WM / 32, FN = WN / 32, KK = BK / 16;
@@ -583,17 +629,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   // the order over all rows, three of the eight XCDs had nothing to do)
   const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM;
   const int nk_all = (K + BK - 1) / BK;
-  int first_tile = blockIdx.x, tile_step = gridDim.x, split = blockIdx.y, per_split = (nk_all + gridDim.y - 1) / gridDim.y;
-  long long split_stride = g.split_stride;
-  if constexpr (LIVE) {
-    const LiveSplits ls = live_splits(M, N, K);
-    if ((int)blockIdx.x >= ls.tiles * ls.splits) return;
-    first_tile = blockIdx.x % ls.tiles;
-    split = blockIdx.x / ls.tiles;
-    tile_step = ls.tiles;   // one tile
-    per_split = ls.per_split;
-    split_stride = ls.stride;
-  }
+  const int split = blockIdx.y, per_split = (nk_all + gridDim.y - 1) / gridDim.y;
   const int kt0 = split * per_split, kt1 = min(nk_all, kt0 + per_split);
   if (kt0 >= kt1) return;
 
@@ -610,13 +646,13 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
     rb = make_rsrc(B, tile_bytes<BKC>(g.ldb, N - n0, K));
   };
   int staged_vb = -1;   // the tile whose first k-tile is already on its way into stage 0 (issued under the previous epilogue)
-  for (int vb = first_tile; vb < tiles_m * tiles_n; vb += tile_step) {
+  for (int vb = blockIdx.x; vb < tiles_m * tiles_n; vb += gridDim.x) {
   int tm, tn;
   tile_of_block(vb, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   if (m0 >= M) continue;
 
-  TC* C = (TC*)g.C + zo * g.c_zo + zi * g.c_zi + (long long)split * split_stride;
+  TC* C = (TC*)g.C + zo * g.c_zo + zi * g.c_zi + (long long)split * g.split_stride;
   __amdgpu_buffer_rsrc_t ra, rb;
   panels(m0, n0, ra, rb);
 
@@ -632,7 +668,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   // window in which their stage is free: LS0 of them right after the barrier (last k16-step of tile t), then up to
   // LS1, LS2, LS3 in total by the first three k16-steps of tile t + 1; the barrier of tile t + 1 needs them landed.
   constexpr int NLD = DA::PER + DB::PER;
-  // Measured (256 x 256 tile, 8 loads per wave): K-contiguous x K-contiguous gains 6-8 % with 2 + 3 + 3 + 0 against all
+  // Measured (on a 256 x 256 tile, 8 loads per wave, which gemm_pp.h has taken over since): K-contiguous x K-contiguous gains 6-8 % with 2 + 3 + 3 + 0 against all
   // 8 at once (per k-tile: 3250 -> 2700 clocks, of which load issue 920 -> 90 and barrier wait 620 -> 310);
   // K-strided operands, whose fragment reads already load the LDS pipe more, do best with the burst.
   constexpr int SPLIT0 = (AKC && BKC) ? 2 : (AKC || BKC) ? 4 : 8, SPLIT1 = (AKC && BKC) ? 5 : 8, SPLIT2 = 8;   // cumulative eighths
@@ -714,7 +750,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   __syncthreads();
 
   // ---- epilogue (as in gemm_mfma_kernel) ----------------------------------------------------------
-  const bool atomic = !LIVE && gridDim.y > 1 && g.split_stride == 0;
+  const bool atomic = gridDim.y > 1 && g.split_stride == 0;
   float* strip = (float*)(lds + STAGE + wave * EP_BYTES);   // behind stage 0, which the next tile is about to use
   const bool vec_ok = gemm_vec_ok(g, epi, C);
   // vector path: 8-column chunk and row-in-pass of this lane, its bias values, and the first pass's prefetch
@@ -725,7 +761,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   // apart, so that each 16-byte store of a wave covers whole 128-byte lines (8 adjacent columns per lane are two stores
   // that each touch half of every line: logits of 4915 x 30522
   // 411 -> 378 us, a dW over 32768 tokens 318 -> 304)
-  constexpr bool F4 = sizeof(TC) == 4 && (EPI == 0 || EPI == EPI_BIAS || LIVE);
+  constexpr bool F4 = sizeof(TC) == 4 && (EPI == 0 || EPI == EPI_BIAS);
   const int c4 = (lane % CPR) * 4;
   float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float csum8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // EPI_COLSUM: this lane's share of its 8 columns' sums
@@ -770,7 +806,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   // The first k-tile of this workgroup's next tile goes into stage 0 now, under the epilogue (issued after the
   // epilogue's own first loads: loads return in order, and the passes must not wait for 64 KB of operands).
   {
-    const int vbn = vb + tile_step;
+    const int vbn = vb + gridDim.x;
     if (vbn < tiles_m * tiles_n) {
       int tmn, tnn;
       tile_of_block(vbn, tiles_m, tiles_n, tmn, tnn);
@@ -826,50 +862,9 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
         const int row = p * RPP + prow;
         const int m = mrow0 + row;
         if (m < M && ncol < N) {
-          float v[8], tt[8];
+          float v[8];
           load8(strip + row * EP_PITCH + c8, v);
-          if (epi & EPI_BIAS) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += bias8[e];
-          }
-          if (epi & EPI_GELU) {
-            if ((epi & EPI_KEEPGRAD) && g.aux_out) {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) gelu_and_grad_epi<E>(v[e], v[e], tt[e]);
-              store8((E*)g.aux_out + (long long)m * g.ldaux + ncol, tt);
-            } else {
-              if (g.aux_out) store8((E*)g.aux_out + (long long)m * g.ldaux + ncol, v);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] = gelu_epi<E>(v[e]);
-            }
-          }
-          if (pre_aux) {
-            unpack8<E>(pre[idx % PD], tt);
-            if (epi & EPI_MULAUX) {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] *= tt[e];
-            } else {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_epi<E>(tt[e]);
-            }
-          }
-          if (epi & EPI_RESID) {
-            if (pre_res) unpack8<E>(pre[idx % PD], tt);
-            else load8((const E*)g.resid + (long long)m * g.ldr + ncol, tt);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += tt[e];
-          }
-          TC* cp = c_lane + (long long)(mrow0 + p * RPP) * g.ldc;
-          if (epi & EPI_ACCUM) {
-            load8(cp, tt);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += tt[e];
-          }
-          store8(cp, v);
-          if (epi & EPI_COLSUM) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) csum8[e] += v[e];
-          }
+          epilogue_pass<E, TC>(g, epi, pre_aux, pre_res, pre[idx % PD], bias8, m, ncol, c_lane + (long long)(mrow0 + p * RPP) * g.ldc, v, csum8);
         }
       });
     } else {

@@ -1,6 +1,7 @@
 // One tile variant of the 16-bit MFMA GEMM (selected with -DL2L_VARIANT=<index>): all four operand
 // layouts, 16-bit and fp32 outputs.
 #include "gemm.h"
+#include "gemm_pp.h"
 #include "gemm_variants.h"
 
 #ifndef L2L_VARIANT
@@ -34,11 +35,29 @@ void launch_layout(const GemmArgs& g, hipStream_t s, int splits) {
 
 }  // namespace
 
+// NST: LDS stages of gemm_mfma_dlds_kernel, or PP: gemm_mfma_pp_kernel
+constexpr int PP = 4;
+
+template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, typename TC, typename E, int NST, int EPI>
+constexpr auto direct_kernel() {
+  if constexpr (NST == PP) {
+    static_assert(BM == 256 && BN == 256 && WM == 128 && WN == 64, "its tile is fixed");
+    return gemm_mfma_pp_kernel<AKC, BKC, TC, E, EPI>;
+  } else {
+    return gemm_mfma_dlds_kernel<BM, BN, WM, WN, AKC, BKC, TC, E, EPI, NST>;
+  }
+}
+template <int BM, int BN, int WM, int WN, int NST>
+constexpr int direct_lds_bytes() {
+  if constexpr (NST == PP) return PP_LDS;
+  else return dlds_lds_bytes<BM, BN, WM, WN, NST>();
+}
+
 template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, typename TC, typename E, int NST, int EPI = -1>
 void launch_direct_one(const GemmArgs& g, hipStream_t s, int splits) {
-  constexpr int LDS = dlds_lds_bytes<BM, BN, WM, WN, NST>();
+  constexpr int LDS = direct_lds_bytes<BM, BN, WM, WN, NST>();
   static_assert(LDS <= 160 * 1024, "tile does not fit the 160 KB LDS");
-  auto kern = gemm_mfma_dlds_kernel<BM, BN, WM, WN, AKC, BKC, TC, E, EPI, NST>;
+  auto kern = direct_kernel<BM, BN, WM, WN, AKC, BKC, TC, E, NST, EPI>();
   static const bool once = [&] {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     return true;
@@ -54,8 +73,8 @@ void launch_direct_one(const GemmArgs& g, hipStream_t s, int splits) {
   hipLaunchKernelGGL(kern, grid, block, LDS, s, g);
 }
 
-// the direct-to-LDS kernel is built for the two layout pairs that carry the layer's work: both operands
-// K-contiguous (forward with transposed weights, dX) and both K-strided (dW)
+// the direct-to-LDS kernels are built for both operands K-contiguous (forward with transposed weights, dX), both K-strided
+// (dW) and A K-contiguous with B K-strided
 template <int BM, int BN, int WM, int WN, typename TC, typename E, int NST>
 void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
   // 16-bit output and both operands K-contiguous: the layer's forward, recompute and dX GEMMs.  Their eight epilogues
@@ -78,10 +97,10 @@ void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
       }
     }
   }
-  if constexpr (sizeof(TC) == 4 && BM == LIVE_TILE && BN == LIVE_TILE) {
+  if constexpr (sizeof(TC) == 4 && NST == PP) {
     if (g.live_splits) {   // A K-contiguous, B K-strided: the head's dX
-      constexpr int LDS = dlds_lds_bytes<BM, BN, WM, WN>();
-      auto kern = gemm_mfma_dlds_kernel<BM, BN, WM, WN, true, false, TC, E, EPI_LIVE_SPLITS>;
+      constexpr int LDS = direct_lds_bytes<BM, BN, WM, WN, NST>();
+      auto kern = direct_kernel<BM, BN, WM, WN, true, false, TC, E, NST, EPI_LIVE_SPLITS>();
       static const bool once = [&] {
         (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         return true;

@@ -1,5 +1,6 @@
 // Tile variants of the bf16 MFMA GEMM: X(index, BM, BN, BK, WM, WN, direct).  direct: the kernel
-// whose global loads go straight into LDS, 1 with two stages, 2 with three (the 64 x 64 tile: both operands K-contiguous only).  Each variant is compiled
+// whose global loads go straight into LDS, 1 with two stages, 2 with three (the 64 x 64 tile: both operands K-contiguous only),
+// 3 the kernel whose two wave groups take turns at the matrix cores.  Each variant is compiled
 // in its own translation unit (gemm_variant.hip with -DL2L_VARIANT=index) so that the build runs in parallel.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -12,7 +13,7 @@
   X(3, 256, 256, 64, 128, 64, 0) \
   X(4, 128, 128, 64, 64, 64, 2) \
   X(5, 64, 64, 64, 32, 32, 1) \
-  X(6, 256, 256, 64, 128, 64, 1) \
+  X(6, 256, 256, 64, 128, 64, 3) \
   X(7, 128, 128, 64, 64, 64, 1) \
   X(8, 256, 128, 64, 64, 64, 2)
 

@@ -1373,3 +1373,16 @@ def test_gemm_64_by_64_tiles(ctx, K):
         assert _gemm_case(ctx, "fp16", impl, 1, 1, M, N, K, bias=True, gelu=True, pad=8) < OUT16["fp16"]
         assert _gemm_case(ctx, "bf16", impl, 1, 1, M, N, K, out_f32=True, pad=3) < 2e-6
         assert _gemm_case(ctx, "fp16", impl, 1, 1, M, N, K, accumulate=True, out_f32=True, pad=8) < 2e-6
+
+
+@pytest.mark.parametrize("K", [8, 64, 72, 136, 200, 264, 328])
+def test_gemm_two_wave_group_tile_k_tile_counts(ctx, K):
+    # 256 x 256 tiles, one to six k-tiles: with one the loads cannot run on into a resident workgroup's next tile, with two
+    # they do so from the first k-tile on, and an odd count leaves the next tile starting in the other stage.  Two by two
+    # ragged tiles in every layout the kernel has, and 21 x 31 tiles, of which a compute unit walks two or three.
+    assert _gemm_case(ctx, "bf16", 106, 1, 1, 264, 392, K, bias=True, resid=True, pad=8) < OUT16["bf16"]
+    assert _gemm_case(ctx, "bf16", 106, 1, 1, 264, 392, K, alpha=0.5, pad=3) < OUT16["bf16"]
+    assert _gemm_case(ctx, "bf16", 106, 1, 0, 264, 392, K, out_f32=True, pad=8) < 2e-6
+    assert _gemm_case(ctx, "fp16", 106, 0, 0, 264, 392, K, out_f32=True, pad=8) < 2e-6
+    assert _gemm_case(ctx, "bf16", 106, 1, 1, 5200, 7704, K, bias=True, pad=8) < OUT16["bf16"]
+    assert _gemm_case(ctx, "bf16", 106, 0, 0, 5200, 7704, K, out_f32=True, accumulate=True, pad=8) < 2e-6

@@ -461,33 +461,33 @@ int variant_for_layout(int v, const GemmArgs& g) {
   return !g.a_kc && g.b_kc ? 3 : v;
 }
 
-// Tile variant and K splits for one launch, by estimated time over the direct-to-LDS tiles.  The figures are measured, in
-// microseconds per k-tile of 64 of one tile: `busy` where as many workgroups as fit (`together`) share each compute unit,
-// `lone` where one is alone on its unit, with few and with all units at work; `rest` is what a tile takes beside its main
-// loop.  Large mini-batches keep the 256 x 256 tile, which has the best rate once it fills the chip (32768 x 4096 x 1024:
-// 242 us against 308 on 256 x 128, 322 on 128 x 128, 460 on 64 x 64); below that the smaller tiles win as soon as it
-// leaves units idle (4096 x 1024 x 4096: 80 us on 64 of its tiles, 50 to 56 on 256 of 128 x 128; 64 x 1024 x 4096: 71
-// against 20 us on 64 x 64).  K splits go through the workspace and cost a second launch and the traffic of their
-// partial sums.  The 128 x 128 tile with three LDS stages (variant 4; K-contiguous operands) is for one workgroup per unit:
+// Tile variant and K splits for one launch, by estimated time over the direct-to-LDS tiles.  The figures are fitted to launches
+// timed one by one, 143 shapes of K-contiguous operands on every tile and 98 of K-strided ones on every tile with 1 to 16 splits
+// (the tile chosen takes on average 0.1 % and 0.5 % longer than the best one, at most 3 and 6 %), in microseconds per k-tile of
+// 64 of one tile: `busy` where as many workgroups as fit (`together`) share each compute unit, `lone` where one is alone on its
+// unit, with few and with all units at work; `rest` is what a tile takes beside its main loop.  Large mini-batches run on the
+// 256 x 256 tile, which has the best rate once it fills the chip (32768 x 4096 x 1024: 205 us against 308 on 256 x 128, 322 on
+// 128 x 128, 460 on 64 x 64); below that the smaller tiles win as soon as it leaves units idle (4096 x 1024 x 4096: 63 us on 64
+// of its tiles, 42 on 256 of 128 x 128 with three stages; 64 x 1024 x 4096: 62 against 19 us on 64 x 64).  Weight gradients,
+// whose K can be split, run on it from about 4000 tokens on (1152 x 4616 x 7000: 91 us over two splits, 111 on 128 x 128 over
+// three; 1024 x 1024 x 32768: 81 against 99).  K splits go through the workspace and cost a second launch and the traffic of
+// their partial sums.  The 128 x 128 tile with three LDS stages (variant 4; K-contiguous operands) is for one workgroup per unit:
 // 4096 x 1024 x 4096 takes 41.8 us against 51.6 with two stages, 4096 x 4096 x 1024, four workgroups per unit, 56.4
 // against 41.6.  Both operands K-strided it gains nothing (66.4 against 66.7 us at 1024 x 4096 x 4096: bound by LDS reads).
 struct TileCost { int v; double busy, lone_few, lone_all, rest; int together; };
-constexpr TileCost kCostKC[] = {{5, 0.225, 0.30, 0.47, 1.5, 4}, {7, 0.60, 0.66, 0.74, 3.0, 2}, {4, 0.69, 0.46, 0.60, 3.0, 1}, {8, 0.88, 0.57, 0.88, 4.5, 1},
-                                {6, 1.58, 1.05, 1.58, 5.8, 1}};
-// ... where the launch accumulates in fp32 (l2l_op_gemm only; the layer's dW operands are K-strided): 256 workgroups of 256 x 128
-// over 8 K splits take 1.3 us per k-tile at 1024 x 1024 x 32768 (98 us; 256 x 256 over 16 splits 83)
-constexpr TileCost kCostKCAccum[] = {kCostKC[0], kCostKC[1], kCostKC[2], {8, 0.88, 0.57, 1.20, 4.5, 1}, {6, 1.58, 1.05, 1.45, 5.8, 1}};
+constexpr TileCost kCostKC[] = {{5, 0.215, 0.25, 0.465, 2.7, 4}, {7, 0.56, 0.525, 0.665, 3.4, 2}, {4, 0.57, 0.465, 0.59, 4.6, 1}, {8, 0.85, 0.55, 0.86, 5.5, 1},
+                                {6, 1.26, 1.04, 1.30, 6.3, 1}};
 // both operands K-strided (dW)
-constexpr TileCost kCostKS[] = {{7, 0.66, 0.92, 1.12, 6.0, 2}, {8, 1.42, 1.14, 1.42, 7.0, 1}, {6, 2.20, 1.70, 2.20, 10.0, 1}};
+constexpr TileCost kCostKS[] = {{7, 0.50, 0.60, 1.10, 3.9, 2}, {8, 1.36, 0.99, 1.32, 5.7, 1}, {6, 1.47, 1.03, 1.40, 4.9, 1}};
 
 // whether an accumulating launch's splits may go through a workspace and split_sum_kernel
 bool split_sum_ok(const GemmArgs& g) { return g.nbatch == 1 && g.N % 8 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0; }
 
 // the rule above over the splits that fit ws_elems, beyond them (`atomics`) over splits that add into C with atomics, which
-// take 4 us per million elements (1024 x 1024 x 32768 over 16 splits: 125 us against 95 through the workspace)
+// take 4 us per million elements (1024 x 1024 x 32768 over 16 splits: 125 us against 95 through the workspace when measured)
 void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool atomics, int* variant, int* splits) {
   const bool colsum = (g.epi & EPI_COLSUM) != 0, can_ws = accum ? split_sum_ok(g) : split_epilogue_ok(g);
-  const TileCost* cost = !g.a_kc ? kCostKS : accum ? kCostKCAccum : kCostKC;
+  const TileCost* cost = g.a_kc ? kCostKC : kCostKS;
   const int ncost = g.a_kc ? 5 : 3;
   const int nk = std::max(1, (g.K + 63) / 64);
   double best = 1e300;
@@ -503,7 +503,7 @@ void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool ato
       const double wgs = (double)tiles * s, per_cu = std::ceil(wgs / 256.0), rounds = std::ceil(per_cu / t.together);
       const double lone = t.lone_few + (t.lone_all - t.lone_few) * std::min(1.0, wgs / 256.0);
       double us = kt * std::max(rounds * lone, per_cu > 1 ? per_cu * t.busy : 0.0) + rounds * t.rest;
-      if (s > 1) us += in_ws ? (accum ? 4.0 : 6.0) + (double)s * g.M * g.N * 8.0 / 4.0e6 : (double)s * g.M * g.N * 4.0e-6;
+      if (s > 1) us += in_ws ? (accum ? 4.3 + (double)s * g.M * g.N * 8.0 / 6.5e6 : 6.0 + (double)s * g.M * g.N * 8.0 / 4.0e6) : (double)s * g.M * g.N * 4.0e-6;
       if (us < best) { best = us; *variant = t.v; *splits = s; }
     }
   }

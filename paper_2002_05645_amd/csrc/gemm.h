@@ -538,12 +538,13 @@ __device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70);
 // ... and until every LDS read this wave issued has returned (vmcnt(0) lgkmcnt(0))
 __device__ __forceinline__ void wait_vm0_lds0() { __builtin_amdgcn_s_waitcnt(0x0070); }
 
-// One pass of the direct-to-LDS kernels' 16-byte epilogue path: 8 columns of row m, v[] = alpha * acc on entry, stored to cp.
+// One pass of the direct-to-LDS kernels' 16-byte epilogue path: 8 columns of a row, v[] = alpha * acc on entry.
 // bias8, csum8: the lane's bias values and column sums; pre: its 16 bytes of the residual or the kept activation, requested
-// some passes earlier (pre_aux / pre_res say which).
-template <typename E, typename TC>
+// some passes earlier (pre_aux / pre_res say which).  live: the row is one of M's (column sums).  io reads and writes the row's other operands: resid(t), old(t) the
+// residual and what C holds, keep(t) stores to aux_out, put(t) to C.
+template <typename E, typename IO>
 __device__ __forceinline__ void epilogue_pass(const GemmArgs& g, int epi, bool pre_aux, bool pre_res, u32x4 pre, const float (&bias8)[8],
-                                              int m, int ncol, TC* cp, float (&v)[8], float (&csum8)[8]) {
+                                              float (&v)[8], float (&csum8)[8], bool live, const IO& io) {
   float tt[8];
   if (epi & EPI_BIAS) {
 #pragma unroll
@@ -553,9 +554,9 @@ __device__ __forceinline__ void epilogue_pass(const GemmArgs& g, int epi, bool p
     if ((epi & EPI_KEEPGRAD) && g.aux_out) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) gelu_and_grad_epi<E>(v[e], v[e], tt[e]);
-      store8((E*)g.aux_out + (long long)m * g.ldaux + ncol, tt);
+      io.keep(tt);
     } else {
-      if (g.aux_out) store8((E*)g.aux_out + (long long)m * g.ldaux + ncol, v);
+      if (g.aux_out) io.keep(v);
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = gelu_epi<E>(v[e]);
     }
@@ -572,21 +573,34 @@ __device__ __forceinline__ void epilogue_pass(const GemmArgs& g, int epi, bool p
   }
   if (epi & EPI_RESID) {
     if (pre_res) unpack8<E>(pre, tt);
-    else load8((const E*)g.resid + (long long)m * g.ldr + ncol, tt);
+    else io.resid(tt);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] += tt[e];
   }
   if (epi & EPI_ACCUM) {
-    load8(cp, tt);
+    io.old(tt);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] += tt[e];
   }
-  store8(cp, v);
+  io.put(v);
   if (epi & EPI_COLSUM) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) csum8[e] += v[e];
+    for (int e = 0; e < 8; ++e) csum8[e] += live ? v[e] : 0.f;
   }
 }
+
+// ... of matrices addressed by 64-bit pointers: 8 columns from (m, ncol) on
+template <typename E, typename TC>
+struct RowIo {
+  const GemmArgs& g;
+  long long m;
+  int ncol;
+  TC* cp;
+  __device__ __forceinline__ void resid(float (&t)[8]) const { load8((const E*)g.resid + m * g.ldr + ncol, t); }
+  __device__ __forceinline__ void old(float (&t)[8]) const { load8(cp, t); }
+  __device__ __forceinline__ void keep(const float (&t)[8]) const { store8((E*)g.aux_out + m * g.ldaux + ncol, t); }
+  __device__ __forceinline__ void put(const float (&t)[8]) const { store8(cp, t); }
+};
 
 // dynamic LDS of gemm_mfma_dlds_kernel: NST stages; the epilogue's strips (one of 32 x (WN + 4) floats per wave) sit
 // behind the first stage, which by then is receiving the next tile
@@ -864,7 +878,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
         if (m < M && ncol < N) {
           float v[8];
           load8(strip + row * EP_PITCH + c8, v);
-          epilogue_pass<E, TC>(g, epi, pre_aux, pre_res, pre[idx % PD], bias8, m, ncol, c_lane + (long long)(mrow0 + p * RPP) * g.ldc, v, csum8);
+          epilogue_pass<E>(g, epi, pre_aux, pre_res, pre[idx % PD], bias8, v, csum8, true, RowIo<E, TC>{g, m, ncol, c_lane + (long long)(mrow0 + p * RPP) * g.ldc});
         }
       });
     } else {

@@ -32,6 +32,8 @@ __device__ __forceinline__ f32x4 mfma_16x16x32(bf16x8 a, bf16x8 b, f32x4 c) {
   }
 }
 
+template <typename T> struct Vec8 { typedef __attribute__((ext_vector_type(8))) T t; };
+
 // One operand part of a stage: ROWS rows (of A) or columns (of B) x 64 k.  HALF (A): local row r is the tile's row
 // (r / 64) * 128 + r % 64, plus what the loads' `extra` bytes come to: the 64 rows of one phase of both wave groups.
 //  KC  (memory [rows, K]):  image [row][64]; the 16-byte chunk c of row r sits at slot c ^ ((r >> 1) & 7): the 16 rows of which
@@ -93,6 +95,65 @@ struct PPPart {
       return __builtin_bit_cast(bf16x8, v);
     }
   }
+};
+
+__device__ __forceinline__ void buf_store16(u32x4 v, __amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)byte_off, 0, 0);
+}
+
+// A wave's 128 x 64 part of a matrix of T in the epilogue: columns col .. col + n - 1 of row prow + `row`, and with n = 4 the
+// same 32 columns on
+template <typename T>
+struct PPOut {
+  __amdgpu_buffer_rsrc_t rs;
+  uint32_t lane0, lane1, pitch;   // this lane's byte offsets (out of range where its columns are past N), bytes from row to row
+  __device__ __forceinline__ PPOut(T* base, long long ld, int m0, int n0, int M, int N, int prow, int col, int n) {
+    const int rows = min(128, M - m0), cols = min(64, N - n0);
+    rs = make_rsrc(base + (long long)m0 * ld + n0, rows > 0 && cols > 0 ? (uint32_t)(((rows - 1) * (uint32_t)ld + cols) * sizeof(T)) : 0u);
+    pitch = (uint32_t)ld * sizeof(T);
+    lane0 = col < cols ? prow * pitch + col * sizeof(T) : BUF_OOB;
+    lane1 = n == 4 && col + 32 < cols ? prow * pitch + (col + 32) * sizeof(T) : BUF_OOB;
+  }
+  __device__ __forceinline__ uint32_t row(int r) const { return (uint32_t)r * pitch; }
+  __device__ __forceinline__ uint32_t off(int r) const { return lane0 + row(r); }
+};
+
+// epilogue_pass's row through them
+template <typename E, typename TC>
+struct PPRowIo {
+  const GemmArgs& g;
+  long long m;
+  int ncol, M, N;
+  const PPOut<TC>& oc;
+  const PPOut<E>& ok;
+  int row;
+  __device__ __forceinline__ void resid(float (&t)[8]) const {   // (beside a kept activation; no epilogue of the layer has both)
+    if (m < M && ncol < N) load8((const E*)g.resid + m * g.ldr + ncol, t);
+  }
+  __device__ __forceinline__ void old(float (&t)[8]) const {
+    
+    if constexpr (sizeof(TC) == 4) {
+      const f32x4 a = __builtin_bit_cast(f32x4, buf_load16(oc.rs, oc.off(row))), b = __builtin_bit_cast(f32x4, buf_load16(oc.rs, oc.off(row) + 16));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { t[e] = a[e]; t[4 + e] = b[e]; }
+    } else {
+      unpack8<TC>(buf_load16(oc.rs, oc.off(row)), t);
+    }
+  }
+  template <typename T>
+  __device__ __forceinline__ static void store(const PPOut<T>& o, int row, const float (&t)[8]) {
+    if constexpr (sizeof(T) == 4) {
+      buf_store16(__builtin_bit_cast(u32x4, f32x4{t[0], t[1], t[2], t[3]}), o.rs, o.off(row));
+      buf_store16(__builtin_bit_cast(u32x4, f32x4{t[4], t[5], t[6], t[7]}), o.rs, o.off(row) + 16);
+    } else {
+      typename Vec8<T>::t a;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a[e] = from_f32<T>(t[e]);
+      buf_store16(__builtin_bit_cast(u32x4, a), o.rs, o.off(row));
+    }
+  }
+  __device__ __forceinline__ void keep(const float (&t)[8]) const { store(ok, row, t); }
+  __device__ __forceinline__ void put(const float (&t)[8]) const { store(oc, row, t); }
 };
 
 constexpr int PP_STAGE = 64 * 1024;                              // A's two parts of 128 rows, B's 256 columns
@@ -164,11 +225,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     ra = make_rsrc(A, live ? tile_bytes<AKC>(g.lda, M - m0, AKC ? K : kend) : 0u);
     rb = make_rsrc(B, live ? tile_bytes<BKC>(g.ldb, N - n0, BKC ? K : kend) : 0u);
   };
-  PA pa;
-  PB pb;
-  pa.init(lda, wm * 64, wave, lane);
-  pb.init(ldb, wn * WN, wave, lane);
-
   __amdgpu_buffer_rsrc_t ra, rb;   // panels that A's first rows and B are being loaded from
   panels(first_tile, ra, rb);
   bool staged = false;   // the tile's first k-tile, and all of the second but A's second rows, are in the two stages
@@ -176,6 +232,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int vb = first_tile; vb < num_tiles; vb += tile_step) {
   __amdgpu_buffer_rsrc_t ra_next, rb_next, ra1 = ra;   // ra1: the same for A's second rows, which come a phase later
   panels(vb + tile_step, ra_next, rb_next);
+  // (computed again for every tile: kept across the epilogues that read a second operand, five or six registers went to
+  // scratch, whose reload waits for the tile's stores)
+  int lane_ = lane;
+  asm volatile("" : "+v"(lane_));
+  PA pa;
+  PB pb;
+  pa.init(lda, wm * 64, wave, lane_);
+  pb.init(ldb, wn * WN, wave, lane_);
 
   f32x4 acc[32];   // [row fragment][column fragment], 16 x 16 each, transposed: lane l holds row l % 16, columns 4 (l / 16) .. + 3
   static_for<0, 32>([&](auto t) { acc[decltype(t)::value] = f32x4{0.f, 0.f, 0.f, 0.f}; });
@@ -216,7 +280,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (kt + 1 == kt1) ra1 = ra_next;
     pa.load(ra1, lda, a_half, (kt + 1 == kt1 && nk > 1 ? kt0 : kt + 1) * BK, kend, nxt + PA::BYTES, wave);
     __builtin_amdgcn_sched_barrier(0);
-    // (the first k-tile's waits were done ahead of the tile; behind an epilogue they would wait for its stores)
+    // (the first k-tile's waits were done ahead of the tile; behind an epilogue they would wait for its stores.  The second
+    // k-tile's can be put off as well, with all of it loaded ahead of the stores: no difference)
     if (kt != kt0) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(NLD) : "memory");   // this k-tile's second rows of A are in
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     pp_barrier();
@@ -255,28 +320,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // a pass is 8 rows, 8 lanes each; a lane keeps its 8 columns through the tile.
   // F4: fp32 results without a 16-bit operand beside them: a lane's columns are two groups of 4, 32 apart, so that each 16-byte
   // store of a wave covers whole 128-byte lines, and its rows are such that the strip's reads do not conflict either
-  constexpr bool F4 = sizeof(TC) == 4 && (EPI == 0 || EPI == EPI_BIAS || LIVE);
+  constexpr bool F4 = sizeof(TC) == 4 && (EPI == 0 || EPI == EPI_BIAS || EPI == EPI_ACCUM || LIVE);
   const int cc = lane & 7;
   const int prow = F4 ? ((lane >> 3) & 1) * 8 + (lane >> 4) : lane >> 3;   // row of the first pass
   constexpr int PSTEP = F4 ? 4 : 8;                                        // rows from a pass to the next
   const int ncol = n0 + cc * 8;
+  // The wave's part of C and of the matrices beside it goes through descriptors that end where its valid rows do, with lanes
+  // past N sent out of range: no pass needs a mask.  (Rows so far apart that a part exceeds 2 GiB go through pointers.)
+  const bool pre_aux = (epi & (EPI_GELUGRAD | EPI_MULAUX)) != 0, pre_res = !pre_aux && (epi & EPI_RESID);
+  constexpr long long FAR = 1LL << 22;
+  const bool far = g.ldc >= FAR || ((epi & EPI_GELU) && g.aux_out && g.ldaux >= FAR) || (pre_aux && g.ldaux >= FAR) || ((epi & EPI_RESID) && g.ldr >= FAR);
+  const PPOut<TC> oc(C, g.ldc, m0, n0, M, N, prow, cc * (F4 ? 4 : 8), F4 ? 4 : 8);
+  const PPOut<E> ok((E*)g.aux_out, g.ldaux, m0, n0, M, N, prow, cc * 8, 8);
+  const PPOut<E> op(pre_aux ? (E*)g.aux : (E*)g.resid, pre_aux ? g.ldaux : g.ldr, m0, n0, M, N, prow, cc * 8, 8);
   float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float csum8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  // one 16-byte operand per pass is requested PD - 1 passes ahead (a load takes longer than a pass; with PD = 6 the residual
-  // epilogue keeps 13 registers in scratch and 32768 x 1024 x 4096 takes 209 us instead of 203)
-  const bool pre_aux = (epi & (EPI_GELUGRAD | EPI_MULAUX)) != 0, pre_res = !pre_aux && (epi & EPI_RESID);
-  constexpr int PD = 4, NP = 16;
-  u32x4 pre[PD];
-  const long long pre_ld = pre_aux ? g.ldaux : g.ldr;
-  const E* pre_lane = (pre_aux ? (const E*)g.aux : (const E*)g.resid) + (long long)prow * pre_ld + ncol;
-  TC* c_lane = C + (long long)prow * g.ldc + ncol;
-  const auto fetch = [&](int ip, u32x4& d) {   // pass ip of the tile
-    const int mu = m0 + (ip / 2) * 16 + (ip % 2) * PSTEP;   // wave-uniform
-    if (mu + prow < M && ncol < N) {
-      if (pre_aux || pre_res) d = *(const u32x4*)(pre_lane + (long long)mu * pre_ld);
-    }
-  };
-  if (vec_ok && !atomic) {
+  if (vec_ok && !atomic && !far) {
     if constexpr (F4) {
       if (epi & EPI_BIAS) {
 #pragma unroll
@@ -286,7 +345,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
       }
     } else if ((epi & EPI_BIAS) && ncol < N) load8((const E*)g.bias + ncol, bias8);
-    static_for<0, PD - 1>([&](auto qc) { fetch(decltype(qc)::value, pre[decltype(qc)::value]); });
   }
   const auto strip_order = [] {   // the wave's own LDS traffic executes in order: this is for the compiler
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -302,11 +360,32 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     strip_order();
   };
   park(std::integral_constant<int, 0>{});
-  static_for<0, 8>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
+  if (vec_ok && !atomic && !far) {
+    // The second operand is requested whole, ahead of the first store: loads and stores complete in one order, and a load
+    // behind a store would come back after that store has reached the L2, a microsecond or two later while all compute units
+    // store.  The 64 registers are the fragments', idle by now.  (32768 x 4096 x 1024 with bias and residual: requested three
+    // passes ahead 273 us, now 251; times a kept activation, with column sums 273 and 256.)
+    // (Flags read at run time: four passes ahead, or the registers do not suffice for whatever they may say.)
+    constexpr int NP = 16, AHEAD = EPI == -1 ? 4 : NP;
+    u32x4 pre[AHEAD];
     __builtin_amdgcn_sched_barrier(0);
-    const int mrow0 = m0 + i * 16;
-    if (vec_ok && !atomic) {
+    if (pre_aux || pre_res) {
+      static_for<0, AHEAD>([&](auto qc) { constexpr int q = decltype(qc)::value; pre[q] = buf_load16(op.rs, op.off(q / 2 * 16 + q % 2 * PSTEP)); });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // fp32 sums that are added to, two such operands per pass: 8 passes ahead (the head's dE, 30522 x 1024 x 4915: 321 us where
+    // each pass asks for its own, now 311)
+    if constexpr (F4 && EPI == EPI_ACCUM) {
+      static_for<0, NP / 2>([&](auto qc) {
+        constexpr int q = decltype(qc)::value, row = q / 2 * 16 + q % 2 * PSTEP;
+        pre[2 * q] = buf_load16(oc.rs, oc.lane0 + oc.row(row));
+        pre[2 * q + 1] = buf_load16(oc.rs, oc.lane1 + oc.row(row));
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    static_for<0, 8>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      __builtin_amdgcn_sched_barrier(0);
       f32x4 sv[4];
       static_for<0, 2>([&](auto pc) {
         constexpr int p = decltype(pc)::value;
@@ -316,48 +395,83 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       });
       strip_order();
       if constexpr (i + 1 < 8) park(std::integral_constant<int, i + 1>{});   // (under the arithmetic and stores of this one)
-      if constexpr (i == 0) wait_vm0();   // the next tile's first stages are in; waited for later they would stand behind the stores
+      if constexpr (i == 0) {   // the next tile's first stages are in; waited for later they would stand behind the stores
+        __builtin_amdgcn_sched_barrier(0);
+        if ((F4 && EPI == EPI_ACCUM) || pre_aux || pre_res) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(AHEAD) : "memory");   // (all but the loads just issued)
+        else wait_vm0();
+        __builtin_amdgcn_sched_barrier(0);
+      }
       static_for<0, 2>([&](auto pc) {
-        constexpr int p = decltype(pc)::value, idx = i * 2 + p;
-        const int m = mrow0 + prow + p * PSTEP;
+        constexpr int p = decltype(pc)::value, row = i * 16 + p * PSTEP;   // row: of the pass, from the wave's first one
+        const int m = m0 + row + prow;
         if constexpr (F4) {
-          float* cp = (float*)C + (long long)m * g.ldc + n0 + cc * 4;
           static_for<0, 2>([&](auto hc) {
             constexpr int hf = decltype(hc)::value;
-            if (m < M && n0 + cc * 4 + hf * 32 < N) {
-              f32x4 v = sv[2 * p + hf];
-              if (epi & EPI_BIAS) v += f32x4{bias8[4 * hf], bias8[4 * hf + 1], bias8[4 * hf + 2], bias8[4 * hf + 3]};
-              *(f32x4*)(cp + hf * 32) = v;
+            f32x4 v = sv[2 * p + hf];
+            if (epi & EPI_BIAS) v += f32x4{bias8[4 * hf], bias8[4 * hf + 1], bias8[4 * hf + 2], bias8[4 * hf + 3]};
+            if constexpr (EPI == EPI_ACCUM) {
+              constexpr int q = 2 * i + p, slot = 2 * (q % (NP / 2)) + hf, row2 = (q + NP / 2) / 2 * 16 + (q + NP / 2) % 2 * PSTEP;
+              v += __builtin_bit_cast(f32x4, pre[slot]);
+              if constexpr (q + NP / 2 < NP) pre[slot] = buf_load16(oc.rs, (hf ? oc.lane1 : oc.lane0) + oc.row(row2));
             }
+            buf_store16(__builtin_bit_cast(u32x4, v), oc.rs, (hf ? oc.lane1 : oc.lane0) + oc.row(row));
           });
         } else {
-          if constexpr (idx + PD - 1 < NP) fetch(idx + PD - 1, pre[(idx + PD - 1) % PD]);
-          if (m < M && ncol < N) {
-            float v[8];
+          float v[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = sv[2 * p + (e >> 2)][e & 3];
-            epilogue_pass<E, TC>(g, epi, pre_aux, pre_res, pre[idx % PD], bias8, m, ncol, c_lane + (long long)(mrow0 + p * PSTEP) * g.ldc, v, csum8);
-          }
+          for (int e = 0; e < 8; ++e) v[e] = sv[2 * p + (e >> 2)][e & 3];
+          constexpr int q = 2 * i + p, next = q + AHEAD;
+          const u32x4 now = pre[q % AHEAD];
+          if constexpr (next < NP)
+            if (pre_aux || pre_res) pre[q % AHEAD] = buf_load16(op.rs, op.off(next / 2 * 16 + next % 2 * PSTEP));
+          epilogue_pass<E>(g, epi, pre_aux, pre_res, now, bias8, v, csum8, m < M, PPRowIo<E, TC>{g, m, ncol, M, N, oc, ok, row});
         }
       });
-    } else {
-      if constexpr (i == 0) wait_vm0();
+    });
+  } else {
+    // splits that add with atomics, rows that are not 16-byte aligned, rows that lie far apart
+    wait_vm0();
+    static_for<0, 8>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      __builtin_amdgcn_sched_barrier(0);
+      const int mrow0 = m0 + i * 16;
+      if (atomic) {   // a row of 64 columns per instruction: two cache lines
+        if constexpr (sizeof(TC) == 4) {
+          float* cp = (float*)C + (long long)mrow0 * g.ldc + n0 + lane;
+          const int rows = n0 + lane < N ? min(16, M - mrow0) : 0;
 #pragma unroll 1
-      for (int u = lane; u < 16 * WN; u += 64) {
-        const int row = u / WN, col = u % WN;
-        const int m = mrow0 + row, n = n0 + col;
-        if (m < M && n < N) {
-          const float v = strip[at(row, col >> 2) + (col & 3)];
-          if constexpr (sizeof(TC) == 4) {
-            if (atomic) { gemm_epilogue_atomic(g, (float*)C, m, n, v); continue; }
+          for (int row = 0; row < 16; ++row)
+            if (row < rows) unsafeAtomicAdd(cp + (long long)row * g.ldc, strip[at(row, lane >> 2) + (lane & 3)]);
+        }
+      } else if (vec_ok) {
+#pragma unroll 1
+        for (int p = 0; p < 2; ++p) {
+          const int row = (lane >> 3) + p * 8, m = mrow0 + row;
+          if (m < M && ncol < N) {
+            float v[8], b8[8];
+            const f32x4 lo = *(const f32x4*)(strip + at(row, 2 * cc)), hi = *(const f32x4*)(strip + at(row, 2 * cc + 1));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
+            if (epi & EPI_BIAS) load8((const E*)g.bias + ncol, b8);
+            u32x4 pre{};
+            if (pre_aux || pre_res) pre = *(const u32x4*)((pre_aux ? (const E*)g.aux + (long long)m * g.ldaux : (const E*)g.resid + (long long)m * g.ldr) + ncol);
+            epilogue_pass<E>(g, epi, pre_aux, pre_res, pre, b8, v, csum8, true, RowIo<E, TC>{g, m, ncol, C + (long long)m * g.ldc + ncol});
           }
-          gemm_epilogue<E, TC>(g, C, m, n, v);   // (EPI_COLSUM is not served here: the host asks for it only when vec_ok holds)
+        }
+      } else {
+#pragma unroll 1
+        for (int u = lane; u < 16 * WN; u += 64) {
+          const int row = u / WN, col = u % WN;
+          const int m = mrow0 + row, n = n0 + col;
+          if (m < M && n < N) {
+            gemm_epilogue<E, TC>(g, C, m, n, strip[at(row, col >> 2) + (col & 3)]);   // (EPI_COLSUM is not served here: the host asks for it only when vec_ok holds)
+          }
         }
       }
       strip_order();
       if constexpr (i + 1 < 8) park(std::integral_constant<int, i + 1>{});
-    }
-  });
+    });
+  }
   if ((epi & EPI_COLSUM) && vec_ok && !atomic) {
     // lanes l, l + 8, l + 16, ... hold the same 8 columns (different rows): fold them; the wave's 64 sums go
     // to its own row of the partial-sum matrix (atomics on the few lines of one [N] vector would queue up at L2)

@@ -115,6 +115,8 @@ void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
     if (g.alpha == 1.0f && g.a_kc && g.b_kc && g.epi == 0) { launch_direct_one<BM, BN, WM, WN, true, true, TC, E, NST, 0>(g, s, splits); return; }
     if constexpr (BM >= 128)
       if (g.alpha == 1.0f && !g.a_kc && !g.b_kc && g.epi == 0) { launch_direct_one<BM, BN, WM, WN, false, false, TC, E, NST, 0>(g, s, splits); return; }
+    if constexpr (NST == PP)   // a dW or the head's dE added to what is there
+      if (g.alpha == 1.0f && !g.a_kc && !g.b_kc && g.epi == EPI_ACCUM && !(splits > 1 && g.split_stride == 0)) { launch_direct_one<BM, BN, WM, WN, false, false, TC, E, NST, EPI_ACCUM>(g, s, splits); return; }
     if constexpr (BM == 256 && BN == 256)
       if (g.alpha == 1.0f && g.a_kc && g.b_kc && g.epi == EPI_BIAS) { launch_direct_one<BM, BN, WM, WN, true, true, TC, E, NST, EPI_BIAS>(g, s, splits); return; }
   }

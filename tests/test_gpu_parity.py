@@ -1386,3 +1386,26 @@ def test_gemm_two_wave_group_tile_k_tile_counts(ctx, K):
     assert _gemm_case(ctx, "fp16", 106, 0, 0, 264, 392, K, out_f32=True, pad=8) < 2e-6
     assert _gemm_case(ctx, "bf16", 106, 1, 1, 5200, 7704, K, bias=True, pad=8) < OUT16["bf16"]
     assert _gemm_case(ctx, "bf16", 106, 0, 0, 5200, 7704, K, out_f32=True, accumulate=True, pad=8) < 2e-6
+
+
+def test_gemm_two_wave_group_tile_rows_far_apart(ctx):
+    # rows of C and of the residual 2^22 + 8 elements apart: a wave's part of them is more than a buffer descriptor covers,
+    # and the epilogue goes through pointers (16-bit with bias and residual; fp32 accumulating)
+    M, N, K, ld = 130, 264, 136, 2 ** 22 + 8
+    g = torch.Generator(device="cuda").manual_seed(3)
+    A, Bm = (torch.randn(s, device="cuda", generator=g).to(torch.bfloat16) for s in ((M, K), (N, K)))
+    bias = torch.randn(N, device="cuda", generator=g).to(torch.bfloat16)
+    ref = A.double() @ Bm.double().t()
+    out, res = (torch.full((M, ld), 7.0, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    res[:, :N] = torch.randn((M, N), device="cuda", generator=g).to(torch.bfloat16)
+    ctx.op_gemm(P.L2L_BF16, False, 1, 1, M, N, K, A, K, Bm, K, out, ld, bias=bias, resid=res, impl=106)
+    want = ref + bias.double() + res[:, :N].double()
+    # fp32 accumulation (2e-6 of the sum of magnitudes) and one rounding to bf16
+    tol = 2e-6 * (A.double().abs() @ Bm.double().abs().t()) + 0.5 * ULP["bf16"] * 1.001 * want.abs()
+    assert bool(((out[:, :N].double() - want).abs() <= tol).all())
+    assert bool((out[:, N:N + 64] == 7).all()) and bool((out[:, -64:] == 7).all())
+    del out, res
+    acc = torch.full((M // 8, ld), 7.0, device="cuda")
+    ctx.op_gemm(P.L2L_BF16, True, 1, 1, M // 8, N, K, A, K, Bm, K, acc, ld, accumulate=True, impl=106)
+    assert bool(((acc[:, :N].double() - ref[:M // 8] - 7).abs() <= tol[:M // 8] + 1e-6).all())
+    assert bool((acc[:, N:N + 64] == 7).all()) and bool((acc[:, -64:] == 7).all())

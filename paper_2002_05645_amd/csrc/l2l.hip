@@ -382,7 +382,8 @@ bool split_epilogue_ok(const GemmArgs& g) {
 // K splits of an fp32 launch: the number with the shortest estimated time.  A compute unit's matrix cores take 0.6 us for a
 // k-tile of 32 (what 100 TFLOP/s over the chip come to); a workgroup alone on its unit waits for its loads, which makes
 // that 0.9 us until two share a unit; splits cost a second launch and the traffic of the partial sums.
-int pick_f32_splits(const GemmArgs& g, size_t ws_elems) {
+// ln: a LayerNorm reads the result, and adds the splits up itself (gemm_then_ln).
+int pick_f32_splits(const GemmArgs& g, size_t ws_elems, bool ln = false) {
   const int nk = std::max(1, (g.K + 31) / 32);
   const long long tiles = (long long)((g.M + F32_TILE - 1) / F32_TILE) * ((g.N + F32_TILE - 1) / F32_TILE) * g.nbatch;
   int best_s = 1;
@@ -393,7 +394,7 @@ int pick_f32_splits(const GemmArgs& g, size_t ws_elems) {
     if (s > 1 && (nk + kt - 1) / kt != s) continue;   // an empty split
     const double per_cu = std::ceil((double)tiles * s / 256.0);
     double us = kt * std::max(per_cu * 0.6, std::ceil(per_cu / 4.0) * 0.9) + 2.0;
-    if (s > 1) us += 3.0 + (double)s * g.M * g.N * 8.0 / 4.0e6;
+    if (s > 1) us += (ln ? 0.5 : 3.0) + (double)s * g.M * g.N * 8.0 / 4.0e6;
     if (us < best) { best = us; best_s = s; }
   }
   return best_s;
@@ -485,7 +486,8 @@ bool split_sum_ok(const GemmArgs& g) { return g.nbatch == 1 && g.N % 8 == 0 && g
 
 // the rule above over the splits that fit ws_elems, beyond them (`atomics`) over splits that add into C with atomics, which
 // take 4 us per million elements (1024 x 1024 x 32768 over 16 splits: 125 us against 95 through the workspace when measured)
-void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool atomics, int* variant, int* splits) {
+// ln: a LayerNorm reads the result, and adds the splits up itself (gemm_then_ln): no launch of their own
+void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool atomics, int* variant, int* splits, bool ln = false) {
   const bool colsum = (g.epi & EPI_COLSUM) != 0, can_ws = accum ? split_sum_ok(g) : split_epilogue_ok(g);
   const TileCost* cost = g.a_kc ? kCostKC : kCostKS;
   const int ncost = g.a_kc ? 5 : 3;
@@ -503,16 +505,16 @@ void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool ato
       const double wgs = (double)tiles * s, per_cu = std::ceil(wgs / 256.0), rounds = std::ceil(per_cu / t.together);
       const double lone = t.lone_few + (t.lone_all - t.lone_few) * std::min(1.0, wgs / 256.0);
       double us = kt * std::max(rounds * lone, per_cu > 1 ? per_cu * t.busy : 0.0) + rounds * t.rest;
-      if (s > 1) us += in_ws ? (accum ? 4.3 + (double)s * g.M * g.N * 8.0 / 6.5e6 : 6.0 + (double)s * g.M * g.N * 8.0 / 4.0e6) : (double)s * g.M * g.N * 4.0e-6;
+      if (s > 1) us += in_ws ? (accum ? 4.3 + (double)s * g.M * g.N * 8.0 / 6.5e6 : (ln ? 1.0 : 6.0) + (double)s * g.M * g.N * 8.0 / 4.0e6) : (double)s * g.M * g.N * 4.0e-6;
       if (us < best) { best = us; *variant = t.v; *splits = s; }
     }
   }
 }
 
-void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant, int* splits) {
+void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant, int* splits, bool ln = false) {
   if (g.a_kc != g.b_kc || g.nbatch != 1 || g.m_dev || g.k_dev) return pick_tile(g, out_f32, variant, splits);
   if (!(out_f32 && g.epi == EPI_ACCUM)) {
-    choose_tile_within(g, false, ws_elems, false, variant, splits);
+    choose_tile_within(g, false, ws_elems, false, variant, splits, ln);
     // (a caller's buffer of column sums may have room for the wider wave tiles that the rule by size takes, and no more)
     if ((g.epi & EPI_COLSUM) && g.colsum_rows > 0 && (g.M + kTiles[*variant].wm - 1) / kTiles[*variant].wm > g.colsum_rows) pick_tile(g, out_f32, variant, splits);
     return;
@@ -572,6 +574,19 @@ void clear_matrix(l2l_ctx* c, const GemmArgs& g) {   // C = 0 (fp32, dense)
   hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks), dim3(256), 0, c->cs, (uint32_t*)g.C, 0u, n);
 }
 
+// the launch's row in the per-shape table, or -1 where nothing is being recorded
+int prof_shape(l2l_ctx* c, const GemmArgs& g, bool out_f32) {
+  if (!c->prof_on) return -1;
+  for (size_t i = 0; i < c->prof_shapes.size(); ++i) {
+    const ProfShape& p = c->prof_shapes[i];
+    if (p.M == g.M && p.N == g.N && p.K == g.K && p.a_kc == g.a_kc && p.b_kc == g.b_kc && p.epi == g.epi && p.out_f32 == (int)out_f32 && p.pass == c->prof_pass) return (int)i;
+  }
+  ProfShape p;
+  p.M = g.M; p.N = g.N; p.K = g.K; p.a_kc = g.a_kc; p.b_kc = g.b_kc; p.epi = g.epi; p.out_f32 = out_f32; p.pass = c->prof_pass;
+  c->prof_shapes.push_back(p);
+  return (int)c->prof_shapes.size() - 1;
+}
+
 // impl: 0 auto, 1 plain, 2 mfma (auto tile), 100 + v: mfma tile variant v (tuning)
 int gemm(l2l_ctx* c, int dtype, bool out_f32, const GemmArgs& g, int impl = 0, int cls = L2L_PROF_GEMM) {
   if (g.M <= 0 || g.N <= 0 || g.nbatch <= 0) return L2L_OK;
@@ -585,19 +600,7 @@ int gemm(l2l_ctx* c, int dtype, bool out_f32, const GemmArgs& g, int impl = 0, i
   const double flops = 2.0 * g.M * g.N * (double)g.K * g.nbatch;
   const double es = esize(dtype);
   const double bytes = ((double)g.M * g.K + (double)g.K * g.N) * es * g.nbatch + (double)g.M * g.N * (out_f32 ? 4 : es) * g.nbatch;
-  int shape = -1;
-  if (c->prof_on && cls == L2L_PROF_GEMM) {   // the launch's row in the per-shape table
-    for (size_t i = 0; i < c->prof_shapes.size() && shape < 0; ++i) {
-      const ProfShape& p = c->prof_shapes[i];
-      if (p.M == g.M && p.N == g.N && p.K == g.K && p.a_kc == g.a_kc && p.b_kc == g.b_kc && p.epi == g.epi && p.out_f32 == (int)out_f32 && p.pass == c->prof_pass) shape = (int)i;
-    }
-    if (shape < 0) {
-      ProfShape p;
-      p.M = g.M; p.N = g.N; p.K = g.K; p.a_kc = g.a_kc; p.b_kc = g.b_kc; p.epi = g.epi; p.out_f32 = out_f32; p.pass = c->prof_pass;
-      c->prof_shapes.push_back(p);
-      shape = (int)c->prof_shapes.size() - 1;
-    }
-  }
+  const int shape = cls == L2L_PROF_GEMM ? prof_shape(c, g, out_f32) : -1;
   const bool fresh = g.fresh && out_f32 && g.epi == EPI_ACCUM;
   GemmArgs gp = g;   // for the kernels without K splits that add: a first result is stored
   if (fresh) gp.epi = 0;
@@ -648,6 +651,43 @@ int ln_fwd(l2l_ctx* c, const void* x, const void* gamma, const void* beta, void*
   return timed(c, L2L_PROF_ROWWISE, 0, 2.0 * rows * n * sizeof(T), [&] {
     hipLaunchKernelGGL(ln_fwd_kernel<T>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, c->cs, (const T*)x, (const T*)gamma,
                        (const T*)beta, (T*)y, mean, rstd, (int)rows, n, eps);
+  });
+}
+
+// whether the LayerNorm behind g may add g's K splits up itself, as far as the shape goes
+bool split_ln_ok(const GemmArgs& g) { return g.epi == (EPI_BIAS | EPI_RESID) && g.N <= SPLIT_LN_MAX && g.N % 8 == 0 && split_epilogue_ok(g); }
+
+// y = LN(g) with g's own result in g.C (needed afterwards only if `keep`).  Where g is worth splitting over K, given that the
+// sum of the splits costs no launch of its own, the LayerNorm adds them up: the small launches, which leave most of the chip
+// idle unsplit (64 x 1024 x 1024: 16 workgroups).  A single sequence of 64 tokens through a layer of 1024: 58.4 us with the
+// sum on its own and the output projection unsplit, now 48.6.
+template <typename T>
+int gemm_then_ln(l2l_ctx* c, const GemmArgs& g, const void* gamma, const void* beta, void* y, float* mean, float* rstd, bool keep) {
+  const int dt = c->cfg.dtype;
+  int v = 0, splits = 1;
+  if (split_ln_ok(g) && c->split_ws && !c->split_atomics && c->force_splits == 0) {
+    if (is16(dt) && mfma_ok(g)) {
+      choose_tile(g, false, c->split_ws_elems, &v, &splits, true);
+      v = variant_for_layout(v, g);
+      if (!kTiles[v].direct) splits = 1;
+    } else if (!is16(dt) && f32_mfma_ok(g)) {
+      splits = pick_f32_splits(g, c->split_ws_elems, true);
+    }
+  }
+  if (splits <= 1) {
+    L2L_TRY(gemm(c, dt, false, g));
+    return ln_fwd<T>(c, g.C, gamma, beta, y, mean, rstd, g.M, g.N, c->cfg.ln_eps);
+  }
+  GemmArgs p = g;
+  p.C = c->split_ws; p.ldc = g.N; p.split_stride = (long long)g.M * g.N; p.epi = 0;
+  p.resident = c->resident_cus;
+  L2L_TRY(timed(c, L2L_PROF_GEMM, 2.0 * g.M * g.N * (double)g.K, ((double)g.M * g.K + (double)g.K * g.N) * esize(dt) + (double)g.M * g.N * 4 * splits, [&] {
+    if (is16(dt)) launch_mfma_variant(v, p, c->cs, splits, true, dt == L2L_FP16);
+    else launch_f32(p, c->cs, splits);
+  }, prof_shape(c, g, false)));
+  return timed(c, L2L_PROF_ROWWISE, 0, (double)g.M * g.N * (4.0 * splits + 2.0 * sizeof(T)), [&] {
+    hipLaunchKernelGGL(split_ln_kernel<T>, dim3(g.M), dim3((g.N + 511) / 512 * 64), 0, c->cs, c->split_ws, splits, g, (const T*)gamma,
+                       (const T*)beta, (T*)y, mean, rstd, c->cfg.ln_eps, (int)keep);
   });
 }
 
@@ -919,9 +959,7 @@ int layer_forward_group(l2l_ctx* c, int slot, const void* x, void* y, int ng, bo
   {
     GemmArgs g = gemm_args((int)M, H, H, c->c, H, 1, W + off[T_WO], wld(H, H), tw, c->r1, H);
     g.epi = EPI_BIAS | EPI_RESID; g.bias = P + off[T_BO]; g.resid = x; g.ldr = H;
-    L2L_TRY(gemm(c, dt, false, g));
-    L2L_TRY(ln_fwd<T>(c, c->r1, P + off[T_G1], P + off[T_BE1], c->y1, keep ? c->mean1 : nullptr, keep ? c->rstd1 : nullptr, M, H,
-                      f.ln_eps));
+    L2L_TRY(gemm_then_ln<T>(c, g, P + off[T_G1], P + off[T_BE1], c->y1, keep ? c->mean1 : nullptr, keep ? c->rstd1 : nullptr, keep));
   }
   // FFN1 + bias + GELU, FFN2 + bias + residual, LayerNorm 2
   {
@@ -933,14 +971,14 @@ int layer_forward_group(l2l_ctx* c, int slot, const void* x, void* y, int ng, bo
     if (keep && skip_ffn2) return L2L_OK;
     GemmArgs h = gemm_args((int)M, H, F, c->ga, F, 1, W + off[T_W2], wld(F, H), tw, c->r2, H);
     h.epi = EPI_BIAS | EPI_RESID; h.bias = P + off[T_B2]; h.resid = c->y1; h.ldr = H;
-    L2L_TRY(gemm(c, dt, false, h));
     if (keep) {
+      L2L_TRY(gemm(c, dt, false, h));
       // backward needs only the statistics of LN2 (y itself was stashed by the forward pass), and the one-pass
       // backward kernel computes them itself
       if (!ln_bwd_one_pass(H))
         L2L_TRY(ln_fwd<T>(c, c->r2, P + off[T_G2], P + off[T_BE2], c->ytmp, c->mean2, c->rstd2, M, H, f.ln_eps));
     } else {
-      L2L_TRY(ln_fwd<T>(c, c->r2, P + off[T_G2], P + off[T_BE2], y, rstd2_out ? c->mean2 : nullptr, rstd2_out, M, H, f.ln_eps));
+      L2L_TRY(gemm_then_ln<T>(c, h, P + off[T_G2], P + off[T_BE2], y, rstd2_out ? c->mean2 : nullptr, rstd2_out, false));
     }
   }
   return L2L_OK;
@@ -1527,6 +1565,12 @@ int l2l_create(const l2l_config* cfg, void* compute_stream, void* copy_stream, l
       if (f32) splits = pick_f32_splits(g, most);
       else choose_tile(g, !kc, most, &v, &splits);
       if (splits > 1) need = std::max(need, (size_t)splits * s[0] * s[1]);
+      if ((i == 1 || i == 3) && h <= SPLIT_LN_MAX) {   // a LayerNorm follows
+        splits = 1;
+        if (f32) splits = pick_f32_splits(g, most, true);
+        else choose_tile(g, false, most, &v, &splits, true);
+        if (splits > 1) need = std::max(need, (size_t)splits * s[0] * s[1]);
+      }
     }
     if (cfg->vocab > 0 && !f32) {
       const GemmArgs h = head_dx_args(c, (int)c->head_rows);

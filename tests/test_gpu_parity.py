@@ -1409,3 +1409,13 @@ def test_gemm_two_wave_group_tile_rows_far_apart(ctx):
     ctx.op_gemm(P.L2L_BF16, True, 1, 1, M // 8, N, K, A, K, Bm, K, acc, ld, accumulate=True, impl=106)
     assert bool(((acc[:, :N].double() - ref[:M // 8] - 7).abs() <= tol[:M // 8] + 1e-6).all())
     assert bool((acc[:, N:N + 64] == 7).all()) and bool((acc[:, -64:] == 7).all())
+
+
+@pytest.mark.parametrize("stats", [False, True])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("hidden,heads", [(8, 1), (256, 4), (520, 1), (1024, 16), (1032, 3), (2048, 32), (2056, 1)])
+def test_layer_few_rows_layernorm_adds_the_splits(hidden, heads, dtype, stats):
+    # 16 tokens: the products in front of both LayerNorms are split over K and the LayerNorm kernel adds the splits up (one
+    # to four waves per row, partly filled ones; from 2056 columns on the two kernels run one after the other)
+    w = S.Workload("few_rows", 1, hidden, heads, 4 * hidden, 8, 50, 1, 2, dtype, 1.0, 900 + hidden)
+    _assert_errs(_layer_case(w, stats=stats, dy_scale=256.0 if dtype == "fp16" else 1.0), TOL[dtype])

@@ -614,7 +614,7 @@ constexpr int dlds_lds_bytes() {
 // the flag tests and the code of the unused operations out of the unrolled epilogue; EPI = -1: flags read from g.epi.
 // NST: LDS stages, 2 or 3.  With three a k-tile's loads are issued two k-tiles ahead, for the tiles whose k-tile is
 // shorter than the way to memory where a workgroup is alone on its compute unit (4096 x 1024 x 4096 on 128 x 128
-// tiles: 51.6 -> 41.8 us; 7000 x 1152 x 4616 on 256 x 128: 94 -> 83 us).
+// tiles: 51.6 -> 41.8 us; 7000 x 1152 x 4616 on 256 x 128: 94 -> 83 us; 1024 x 1024 x 4096 on 64 x 64: 32.8 -> 19.7 us).
 template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, typename TC, typename E = bf16, int EPI = -1, int NST = 2>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_kernel(GemmArgs g) {
   constexpr int BK = 64;

@@ -12,7 +12,7 @@
   X(2, 256, 128, 64, 64, 64, 0) \
   X(3, 256, 256, 64, 128, 64, 0) \
   X(4, 128, 128, 64, 64, 64, 2) \
-  X(5, 64, 64, 64, 32, 32, 1) \
+  X(5, 64, 64, 64, 32, 32, 2) \
   X(6, 256, 256, 64, 128, 64, 3) \
   X(7, 128, 128, 64, 64, 64, 1) \
   X(8, 256, 128, 64, 64, 64, 2)

@@ -469,14 +469,17 @@ int variant_for_layout(int v, const GemmArgs& g) {
 // unit, with few and with all units at work; `rest` is what a tile takes beside its main loop.  Large mini-batches run on the
 // 256 x 256 tile, which has the best rate once it fills the chip (32768 x 4096 x 1024: 205 us against 308 on 256 x 128, 322 on
 // 128 x 128, 460 on 64 x 64); below that the smaller tiles win as soon as it leaves units idle (4096 x 1024 x 4096: 63 us on 64
-// of its tiles, 42 on 256 of 128 x 128 with three stages; 64 x 1024 x 4096: 62 against 19 us on 64 x 64).  Weight gradients,
+// of its tiles, 42 on 256 of 128 x 128 with three stages; 64 x 1024 x 4096: 62 against 17 us on 64 x 64).  Weight gradients,
 // whose K can be split, run on it from about 4000 tokens on (1152 x 4616 x 7000: 91 us over two splits, 111 on 128 x 128 over
 // three; 1024 x 1024 x 32768: 81 against 99).  K splits go through the workspace and cost a second launch and the traffic of
 // their partial sums.  The 128 x 128 tile with three LDS stages (variant 4; K-contiguous operands) is for one workgroup per unit:
 // 4096 x 1024 x 4096 takes 41.8 us against 51.6 with two stages, 4096 x 4096 x 1024, four workgroups per unit, 56.4
 // against 41.6.  Both operands K-strided it gains nothing (66.4 against 66.7 us at 1024 x 4096 x 4096: bound by LDS reads).
+// The 64 x 64 tile (variant 5) has three stages throughout, 48 KB of LDS, three workgroups per unit: 1024 x 1024 x 4096 takes
+// 19.7 us against 32.8 with two, 64 x 1024 x 1024 6.9 against 7.6; from eight workgroups per unit on it loses (2048 x 4096 x 1024
+// 33.1 against 29.6), where 128 x 128 takes 23.
 struct TileCost { int v; double busy, lone_few, lone_all, rest; int together; };
-constexpr TileCost kCostKC[] = {{5, 0.215, 0.25, 0.465, 2.7, 4}, {7, 0.56, 0.525, 0.665, 3.4, 2}, {4, 0.57, 0.465, 0.59, 4.6, 1}, {8, 0.85, 0.55, 0.86, 5.5, 1},
+constexpr TileCost kCostKC[] = {{5, 0.20, 0.205, 0.27, 3.6, 3}, {7, 0.56, 0.525, 0.665, 3.4, 2}, {4, 0.57, 0.465, 0.59, 4.6, 1}, {8, 0.85, 0.55, 0.86, 5.5, 1},
                                 {6, 1.26, 1.04, 1.30, 6.3, 1}};
 // both operands K-strided (dW)
 constexpr TileCost kCostKS[] = {{7, 0.50, 0.60, 1.10, 3.9, 2}, {8, 1.36, 0.99, 1.32, 5.7, 1}, {6, 1.47, 1.03, 1.40, 4.9, 1}};

@@ -1419,3 +1419,12 @@ def test_layer_few_rows_layernorm_adds_the_splits(hidden, heads, dtype, stats):
     # to four waves per row, partly filled ones; from 2056 columns on the two kernels run one after the other)
     w = S.Workload("few_rows", 1, hidden, heads, 4 * hidden, 8, 50, 1, 2, dtype, 1.0, 900 + hidden)
     _assert_errs(_layer_case(w, stats=stats, dy_scale=256.0 if dtype == "fp16" else 1.0), TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("K", [8, 64, 72, 136, 200, 264, 328])
+def test_gemm_small_tile_three_stages_k_tile_counts(ctx, K, dtype):
+    # 64 x 64 tiles, one to six k-tiles through three LDS stages, ragged edges, both output types and epilogue paths
+    assert _gemm_case(ctx, dtype, 105, 1, 1, 200, 136, K, bias=True, resid=True, pad=8) < OUT16[dtype]
+    assert _gemm_case(ctx, dtype, 105, 1, 1, 65, 72, K, bias=True, gelu=True, alpha=0.5, pad=3) < OUT16[dtype]
+    assert _gemm_case(ctx, dtype, 105, 1, 1, 200, 136, K, out_f32=True, pad=8) < 2e-6

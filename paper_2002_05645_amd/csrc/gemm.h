@@ -31,6 +31,30 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, long lon
   *c = from_f32<TC>(v);
 }
 
+// The same for rows m .. m + live - 1 (1 to R of them) of one column.  The rows' operands are requested together, ahead of the
+// first store (a load behind a store waits for it), and each flag is tested once.  4096 x 4100 x 1024 on 256 x 256 tiles, an element at
+// a time and four rows together: bias and residual 198 and 88 us, GELU' 198 and 164, none 77 and 56.
+template <int R, typename T, typename TC>
+__device__ __forceinline__ void gemm_epilogue_rows(const GemmArgs& g, int epi, TC* C, long long m, long long n, int live, float bias, float (&v)[R]) {
+  float aux[R], res[R], old[R];
+  const auto each = [&](auto&& f) {
+    static_for<0, R>([&](auto rc) { f(decltype(rc)::value, m + min((int)decltype(rc)::value, live - 1)); });
+  };
+  if (epi & (EPI_GELUGRAD | EPI_MULAUX)) each([&](int r, long long row) { aux[r] = to_f32(((const T*)g.aux)[row * g.ldaux + n]); });
+  if (epi & EPI_RESID) each([&](int r, long long row) { res[r] = to_f32(((const T*)g.resid)[row * g.ldr + n]); });
+  if (epi & EPI_ACCUM) each([&](int r, long long row) { old[r] = to_f32(C[row * g.ldc + n]); });
+  if (epi & EPI_BIAS) each([&](int r, long long) { v[r] += bias; });
+  if (epi & EPI_GELU) {
+    if (g.aux_out) each([&](int r, long long row) { if (r < live) ((T*)g.aux_out)[row * g.ldaux + n] = from_f32<T>((epi & EPI_KEEPGRAD) ? gelu_grad_f(v[r]) : v[r]); });
+    each([&](int r, long long) { v[r] = gelu_f(v[r]); });
+  }
+  if (epi & EPI_GELUGRAD) each([&](int r, long long) { v[r] *= gelu_grad_f(aux[r]); });
+  if (epi & EPI_MULAUX) each([&](int r, long long) { v[r] *= aux[r]; });
+  if (epi & EPI_RESID) each([&](int r, long long) { v[r] += res[r]; });
+  if (epi & EPI_ACCUM) each([&](int r, long long) { v[r] += old[r]; });
+  each([&](int r, long long row) { if (r < live) C[row * g.ldc + n] = from_f32<TC>(v[r]); });
+}
+
 // ------------------------------------------------------------------------------------------------
 // Plain kernel: 64x64 tile, 256 threads, 4x4 outputs per thread, fp32 FMA.
 template <typename T, typename TC>

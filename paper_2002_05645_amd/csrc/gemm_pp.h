@@ -170,12 +170,13 @@ __device__ __forceinline__ void pp_barrier() {
 // EPI = EPI_LIVE_SPLITS: fp32 partial results of a K split whose factor follows from the rows that *m_dev says are live
 // (live_splits): a grid of LIVE_WGS workgroups, of which tile count x splits have work, one tile each, no epilogue.
 constexpr int EPI_LIVE_SPLITS = -2;
+// EPI = EPI_SCALED: alpha times the product and nothing else
+constexpr int EPI_SCALED = -3;
 template <bool AKC, bool BKC, typename TC, typename E, int EPI>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_mfma_pp_kernel(GemmArgs g) {
   constexpr int BM = 256, BN = 256, BK = 64, WM = 128, WN = 64;
   constexpr bool LIVE = EPI == EPI_LIVE_SPLITS;
-  const int epi = EPI >= 0 ? EPI : LIVE ? 0 : g.epi;
-  const float alpha = EPI >= 0 ? 1.0f : g.alpha;   // the launcher sends only alpha = 1 to the kernels with compiled-in flags
+  const int epi = EPI >= 0 ? EPI : EPI == -1 ? g.epi : 0;
   using PA = PPPart<128, AKC, true>;
   using PB = PPPart<256, BKC, false>;
   static_assert(2 * PA::BYTES + PB::BYTES == PP_STAGE, "stage");
@@ -320,7 +321,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // a pass is 8 rows, 8 lanes each; a lane keeps its 8 columns through the tile.
   // F4: fp32 results without a 16-bit operand beside them: a lane's columns are two groups of 4, 32 apart, so that each 16-byte
   // store of a wave covers whole 128-byte lines, and its rows are such that the strip's reads do not conflict either
-  constexpr bool F4 = sizeof(TC) == 4 && (EPI == 0 || EPI == EPI_BIAS || EPI == EPI_ACCUM || LIVE);
+  constexpr bool F4 = sizeof(TC) == 4 && (EPI == 0 || EPI == EPI_BIAS || EPI == EPI_ACCUM || EPI == EPI_SCALED || LIVE);
   const int cc = lane & 7;
   const int prow = F4 ? ((lane >> 3) & 1) * 8 + (lane >> 4) : lane >> 3;   // row of the first pass
   constexpr int PSTEP = F4 ? 4 : 8;                                        // rows from a pass to the next
@@ -355,10 +356,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr int i = decltype(ic)::value;
     static_for<0, 4>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
-      *(f32x4*)(strip + at(lane & 15, j * 4 + (lane >> 4))) = alpha * acc[i * 4 + j];
+      *(f32x4*)(strip + at(lane & 15, j * 4 + (lane >> 4))) = acc[i * 4 + j];
     });
     strip_order();
   };
+  if constexpr (EPI == -1 || EPI == EPI_SCALED) {   // (here and not as the strips are filled: two to five registers less)
+    if (g.alpha != 1.0f) static_for<0, 32>([&](auto t) { acc[decltype(t)::value] *= g.alpha; });
+  }
   park(std::integral_constant<int, 0>{});
   if (vec_ok && !atomic && !far) {
     // The second operand is requested whole, ahead of the first store: loads and stores complete in one order, and a load
@@ -459,12 +463,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           }
         }
       } else {
+        // (EPI_COLSUM is not served here: the host asks for it only when vec_ok holds)
+        const int n = n0 + lane, rows = min(16, M - mrow0);
+        if (n < N) {
+          const float bias = (epi & EPI_BIAS) ? to_f32(((const E*)g.bias)[n]) : 0.f;
 #pragma unroll 1
-        for (int u = lane; u < 16 * WN; u += 64) {
-          const int row = u / WN, col = u % WN;
-          const int m = mrow0 + row, n = n0 + col;
-          if (m < M && n < N) {
-            gemm_epilogue<E, TC>(g, C, m, n, strip[at(row, col >> 2) + (col & 3)]);   // (EPI_COLSUM is not served here: the host asks for it only when vec_ok holds)
+          for (int row = 0; row < rows; row += 4) {
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = strip[at(row + r, lane >> 2) + (lane & 3)];
+            gemm_epilogue_rows<4, E, TC>(g, epi, C, mrow0 + row, n, min(4, rows - row), bias, v);
           }
         }
       }

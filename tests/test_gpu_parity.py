@@ -170,9 +170,9 @@ EPILOGUES = {0: dict(), 1: dict(bias=True), 9: dict(bias=True, resid=True), 3: d
 
 
 def _gemm_ex_case(ctx, dtype, M, N, K, bias=False, resid=False, gelu=False, gelugrad=False, colsum=False, a_kc=1, b_kc=1,
-                  out_f32=False, accumulate=False, seed=0, keepgrad=False, mulaux=False):
-    """One l2l_op_gemm_ex launch (library's choice of kernel) checked ELEMENT BY ELEMENT against
-    epilogue(rounded(A) @ rounded(B)) in fp64.  Bounds per element: an fp32 output may differ by the fp32
+                  out_f32=False, accumulate=False, seed=0, keepgrad=False, mulaux=False, impl=0, alpha=1.0):
+    """One l2l_op_gemm_ex launch (impl 0: library's choice of kernel) checked ELEMENT BY ELEMENT against
+    epilogue(alpha rounded(A) @ rounded(B)) in fp64.  Bounds per element: an fp32 output may differ by the fp32
     accumulation error (2e-6 of the row-times-column magnitude); a 16-bit output additionally by one rounding to the
     format (half a unit in the last place, ULP / 2 relative).  The 16-bit epilogues evaluate Phi(u) and gelu'(u) by
     polynomials with absolute errors below 4e-5 and 2e-4 (pinned on the CPU), which enter as 5e-5 |u| and 2.5e-4 |acc|."""
@@ -184,8 +184,8 @@ def _gemm_ex_case(ctx, dtype, M, N, K, bias=False, resid=False, gelu=False, gelu
     Bd = to_dev(np.ascontiguousarray(Bm.T) if b_kc else Bm, dtype)
     lda, ldb = (K if a_kc else M), (K if b_kc else N)
     Ar, Br = rounded(A, dtype), rounded(Bm, dtype)
-    acc = Ar @ Br
-    scale = np.abs(Ar) @ np.abs(Br)                         # magnitude of the sum of products, per output
+    acc = alpha * (Ar @ Br)
+    scale = abs(alpha) * (np.abs(Ar) @ np.abs(Br))          # magnitude of the sum of products, per output
     tol = 2e-6 * scale
     ref = acc.copy()
     kw = dict(epi=0)
@@ -225,7 +225,7 @@ def _gemm_ex_case(ctx, dtype, M, N, K, bias=False, resid=False, gelu=False, gelu
     if colsum:
         csd = torch.full((cs_rows + 1, N), 12345.0, device="cuda")      # one canary row behind what may be written
         kw.update(epi=kw["epi"] | B.EPI_COLSUM, colsum=csd, colsum_rows=cs_rows)
-    used = ctx.op_gemm_ex(DT[dtype], f32out, a_kc, b_kc, M, N, K, Ad, lda, Bd, ldb, Cd, ldc, 1.0, impl=0, **kw)
+    used = ctx.op_gemm_ex(DT[dtype], f32out, a_kc, b_kc, M, N, K, Ad, lda, Bd, ldb, Cd, ldc, alpha, impl=impl, **kw)
     torch.cuda.synchronize()
     got = to_host(Cd)
     assert np.array_equal(got[:, N:], C0v[:, N:]), "wrote outside the N columns"
@@ -1386,6 +1386,22 @@ def test_gemm_two_wave_group_tile_k_tile_counts(ctx, K):
     assert _gemm_case(ctx, "fp16", 106, 0, 0, 264, 392, K, out_f32=True, pad=8) < 2e-6
     assert _gemm_case(ctx, "bf16", 106, 1, 1, 5200, 7704, K, bias=True, pad=8) < OUT16["bf16"]
     assert _gemm_case(ctx, "bf16", 106, 0, 0, 5200, 7704, K, out_f32=True, accumulate=True, pad=8) < 2e-6
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("M,N", [(1, 257), (131, 259), (270, 264)])
+def test_gemm_two_wave_group_tile_general_epilogues_elementwise(ctx, dtype, M, N):
+    # 256 x 256 tiles: rows that allow no 16-byte access (N = 257 and 259: columns one by one, rows by fours with one to three
+    # left over), through compiled-in flags and flags read at run time, and the scaled product, which has a kernel of its own
+    # where nothing else is asked for, aligned and not
+    for K in (64, 136):
+        kw = dict(seed=M + N + K, impl=106)
+        for epi in (0, 1, 9, 3, 67, 4, 128, 8):
+            _gemm_ex_case(ctx, dtype, M, N, K, **EPILOGUES[epi], **kw)
+        _gemm_ex_case(ctx, dtype, M, N, K, alpha=0.5, **kw)
+        _gemm_ex_case(ctx, dtype, M, N, K, alpha=-3.0, bias=True, resid=True, **kw)
+        for f32 in (dict(), dict(bias=True), dict(resid=True), dict(accumulate=True), dict(alpha=0.5), dict(alpha=0.5, accumulate=True)):
+            _gemm_ex_case(ctx, dtype, M, N, K, out_f32=True, **f32, **kw)
 
 
 def test_gemm_two_wave_group_tile_rows_far_apart(ctx):

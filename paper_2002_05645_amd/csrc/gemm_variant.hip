@@ -156,6 +156,13 @@ typedef bf16 Elem;
 #endif
 
 void L2L_LAUNCH_NAME(const GemmArgs& g, hipStream_t s, int splits, bool out_f32) {
+  if constexpr (kThis.direct && kThis.bm == 64) {
+    if (small_tile_two_stages(g.M, g.N, g.K, g.nbatch, out_f32 ? splits : 1)) {
+      if (out_f32) launch_direct<kThis.bm, kThis.bn, kThis.wm, kThis.wn, float, Elem, 2>(g, s, splits);
+      else launch_direct<kThis.bm, kThis.bn, kThis.wm, kThis.wn, Elem, Elem, 2>(g, s, 1);
+      return;
+    }
+  }
   if constexpr (kThis.direct) {   // callers pick these variants for every layout pair but (A K-strided, B K-contiguous)
     if (out_f32) launch_direct<kThis.bm, kThis.bn, kThis.wm, kThis.wn, float, Elem, kThis.direct + 1>(g, s, splits);
     else launch_direct<kThis.bm, kThis.bn, kThis.wm, kThis.wn, Elem, Elem, kThis.direct + 1>(g, s, 1);

@@ -1438,9 +1438,17 @@ def test_layer_few_rows_layernorm_adds_the_splits(hidden, heads, dtype, stats):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
-@pytest.mark.parametrize("K", [8, 64, 72, 136, 200, 264, 328])
+@pytest.mark.parametrize("K", [8, 64, 72, 136, 200, 264, 320, 328, 384, 392, 456, 520, 1032])
 def test_gemm_small_tile_three_stages_k_tile_counts(ctx, K, dtype):
-    # 64 x 64 tiles, one to six k-tiles through three LDS stages, ragged edges, both output types and epilogue paths
+    # 64 x 64 tiles, ragged edges, both output types and epilogue paths: one to five k-tiles through two LDS stages, six to
+    # seventeen through three
     assert _gemm_case(ctx, dtype, 105, 1, 1, 200, 136, K, bias=True, resid=True, pad=8) < OUT16[dtype]
     assert _gemm_case(ctx, dtype, 105, 1, 1, 65, 72, K, bias=True, gelu=True, alpha=0.5, pad=3) < OUT16[dtype]
     assert _gemm_case(ctx, dtype, 105, 1, 1, 200, 136, K, out_f32=True, pad=8) < 2e-6
+
+
+@pytest.mark.parametrize("M,N", [(1536, 2048), (1537, 2048), (2048, 2048), (2049, 2048)])
+def test_gemm_small_tile_stages_by_workgroups(ctx, M, N):
+    # 64 x 64 tiles with six and seven k-tiles: 768 workgroups and 1056 go through three LDS stages, 800 and 1024 through two
+    _gemm_ex_case(ctx, "bf16", M, N, 384, impl=105, seed=M, **EPILOGUES[9])
+    _gemm_ex_case(ctx, "fp16", M, N, 392, impl=105, seed=M, **EPILOGUES[67])

@@ -462,38 +462,53 @@ int variant_for_layout(int v, const GemmArgs& g) {
   return !g.a_kc && g.b_kc ? 3 : v;
 }
 
-// Tile variant and K splits for one launch, by estimated time over the direct-to-LDS tiles.  The figures are fitted to launches
-// timed one by one, 143 shapes of K-contiguous operands on every tile and 98 of K-strided ones on every tile with 1 to 16 splits
-// (the tile chosen takes on average 0.1 % and 0.5 % longer than the best one, at most 3 and 6 %), in microseconds per k-tile of
-// 64 of one tile: `busy` where as many workgroups as fit (`together`) share each compute unit, `lone` where one is alone on its
-// unit, with few and with all units at work; `rest` is what a tile takes beside its main loop.  Large mini-batches run on the
-// 256 x 256 tile, which has the best rate once it fills the chip (32768 x 4096 x 1024: 205 us against 308 on 256 x 128, 322 on
-// 128 x 128, 460 on 64 x 64); below that the smaller tiles win as soon as it leaves units idle (4096 x 1024 x 4096: 63 us on 64
-// of its tiles, 42 on 256 of 128 x 128 with three stages; 64 x 1024 x 4096: 62 against 17 us on 64 x 64).  Weight gradients,
-// whose K can be split, run on it from about 4000 tokens on (1152 x 4616 x 7000: 91 us over two splits, 111 on 128 x 128 over
-// three; 1024 x 1024 x 32768: 81 against 99).  K splits go through the workspace and cost a second launch and the traffic of
+// Tile variant and K splits for one launch, by estimated time over the direct-to-LDS tiles.  The figures, in microseconds, are
+// fitted to launches timed one by one on every tile, with up to 32 splits.  Per k-tile of 64 of one tile: `busy` where as many
+// workgroups as fit (`together`) share each compute unit, `lone` where one is alone on its unit, with few and with all units at
+// work.  `rest` is what a tile takes beside its main loop; `second`, `f32`, `accum` and `element` come on top of it where the
+// epilogue reads or writes a second matrix, stores fp32 results (K splits do), adds to them, and goes element by element (outputs
+// that allow no 16-byte access).  Accumulating launches of K-contiguous operands have rows of their own: 256 workgroups of 256 x 128
+// over K splits take 1.2 to 1.3 us per k-tile, not 0.9 (2048 x 1024 x 12288: 77 us over four of them, 61 on 256 x 256 over six).
+// What the chosen tile takes over the best one, on average and at most, over the shapes that the figures were fitted to:
+//   K-contiguous   unsplit 0.1 and 18 % (168 shapes, six epilogues), splits allowed 0.5 and 15 % (160, three epilogues), odd widths
+//                  0.9 and 37 % (33, six epilogues), accumulating 2.4 and 20 % (209), with atomics 1.4 and 25 % (95)
+//   K-strided      unsplit 0.0 and 4 % (103, two output types), splits allowed 1.1 and 25 % (116, two output types), accumulating
+//                  1.8 and 39 % (414; above 5 % in one of eight, the worst with a few hundred columns and K above 10000), with
+//                  atomics 3.0 and 16 % (95)
+// Large mini-batches run on the 256 x 256 tile, which has the best rate once it fills the chip (32768 x 4096 x 1024: 205 us against
+// 308 on 256 x 128, 322 on 128 x 128, 460 on 64 x 64); below that the smaller tiles win as soon as it leaves units idle (4096 x 1024
+// x 4096: 63 us on 64 of its tiles, 42 on 256 of 128 x 128 with three stages; 64 x 1024 x 4096: 62 against 17 us on 64 x 64).  Weight
+// gradients, whose K can be split, run on it from about 4000 tokens on (1152 x 4616 x 7000: 91 us over two splits, 111 on 128 x 128
+// over three; 1024 x 1024 x 32768: 81 against 99).  K splits go through the workspace and cost a second launch and the traffic of
 // their partial sums.  The 128 x 128 tile with three LDS stages (variant 4; K-contiguous operands) is for one workgroup per unit:
 // 4096 x 1024 x 4096 takes 41.8 us against 51.6 with two stages, 4096 x 4096 x 1024, four workgroups per unit, 56.4
 // against 41.6.  Both operands K-strided it gains nothing (66.4 against 66.7 us at 1024 x 4096 x 4096: bound by LDS reads).
-// The 64 x 64 tile (variant 5) has three stages throughout, 48 KB of LDS, three workgroups per unit: 1024 x 1024 x 4096 takes
-// 19.7 us against 32.8 with two, 64 x 1024 x 1024 6.9 against 7.6; from eight workgroups per unit on it loses (2048 x 4096 x 1024
-// 33.1 against 29.6), where 128 x 128 takes 23.
-struct TileCost { int v; double busy, lone_few, lone_all, rest; int together; };
-constexpr TileCost kCostKC[] = {{5, 0.20, 0.205, 0.27, 3.6, 3}, {7, 0.56, 0.525, 0.665, 3.4, 2}, {4, 0.57, 0.465, 0.59, 4.6, 1}, {8, 0.85, 0.55, 0.86, 5.5, 1},
-                                {6, 1.26, 1.04, 1.30, 6.3, 1}};
+// The 64 x 64 tile (variant 5) has three stages or two by small_tile_two_stages, one row for each.
+struct TileCost { int v; double busy, lone_few, lone_all, rest; int together; double second, f32, accum, element; };
+constexpr TileCost kCostKC[] = {{5, 0.212, 0.211, 0.231, 3.632, 3, 0.36, 0.50, 0, 3.57}, {5, 0.226, 0.400, 0.500, 4.399, 4, 0, 0, 0, 2.94},
+                                {7, 0.565, 0.423, 0.751, 4.486, 2, 1.00, 0.99, 0, 15.65}, {4, 0.582, 0.401, 0.582, 5.751, 1, 0.67, 0, 0, 9.39},
+                                {8, 0.914, 0.525, 0.914, 6.218, 1, 1.00, 2.72, 0, 17.11}, {6, 1.270, 0.559, 1.270, 8.117, 1, 3.53, 1.60, 0, 14.59}};
+// ... where the launch adds to C in fp32
+constexpr TileCost kCostKCAccum[] = {{5, 0.208, 0.226, 0.226, 3.620, 3, 0, 0.98, 1.14, 6.21}, {5, 0.248, 0.217, 0.217, 5.220, 4, 0, 0, 0.41, 4.28},
+                                     {7, 0.478, 0.519, 0.715, 4.828, 2, 0, 0, 5.91, 26.38}, {4, 0.577, 0.324, 0.577, 6.053, 1, 0, 0, 4.87, 12.88},
+                                     {8, 0.936, 0.418, 0.936, 6.256, 1, 0, 0.35, 6.68, 22.29}, {6, 1.306, 0.465, 1.306, 4.293, 1, 0, 0.53, 7.31, 23.15}};
 // both operands K-strided (dW)
-constexpr TileCost kCostKS[] = {{7, 0.50, 0.60, 1.10, 3.9, 2}, {8, 1.36, 0.99, 1.32, 5.7, 1}, {6, 1.47, 1.03, 1.40, 4.9, 1}};
+constexpr TileCost kCostKS[] = {{7, 0.514, 0.541, 0.932, 5.843, 2, 0, 0, 3.64, 15.65}, {8, 1.161, 1.161, 1.161, 6.003, 1, 0, 0, 4.49, 17.11},
+                                {6, 1.070, 1.037, 1.070, 6.217, 1, 0, 0, 4.33, 14.59}};
 
 // whether an accumulating launch's splits may go through a workspace and split_sum_kernel
 bool split_sum_ok(const GemmArgs& g) { return g.nbatch == 1 && g.N % 8 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0; }
 
 // the rule above over the splits that fit ws_elems, beyond them (`atomics`) over splits that add into C with atomics, which
-// take 4 us per million elements (1024 x 1024 x 32768 over 16 splits: 125 us against 95 through the workspace when measured)
+// take 2.9 us per million elements (1024 x 1024 x 32768 over 16 splits: 125 us against 95 through the workspace when measured).
+// Of the workspace's figures the first is its launch, the second what each slice adds to a thread's chain of loads, the third
+// its traffic.
 // ln: a LayerNorm reads the result, and adds the splits up itself (gemm_then_ln): no launch of their own
-void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool atomics, int* variant, int* splits, bool ln = false) {
-  const bool colsum = (g.epi & EPI_COLSUM) != 0, can_ws = accum ? split_sum_ok(g) : split_epilogue_ok(g);
-  const TileCost* cost = g.a_kc ? kCostKC : kCostKS;
-  const int ncost = g.a_kc ? 5 : 3;
+void choose_tile_within(const GemmArgs& g, bool out_f32, bool accum, size_t ws_elems, bool atomics, int* variant, int* splits, bool ln = false) {
+  const bool colsum = (g.epi & EPI_COLSUM) != 0, element = !gemm_vec_ok(g, g.epi, g.C);
+  const bool second = (g.epi & (EPI_RESID | EPI_MULAUX | EPI_GELUGRAD)) != 0 || ((g.epi & EPI_GELU) && g.aux_out), can_ws = accum ? split_sum_ok(g) : split_epilogue_ok(g);
+  const TileCost* cost = !g.a_kc ? kCostKS : out_f32 && (g.epi & EPI_ACCUM) ? kCostKCAccum : kCostKC;
+  const int ncost = g.a_kc ? 6 : 3;
   const int nk = std::max(1, (g.K + 63) / 64);
   double best = 1e300;
   for (int i = 0; i < ncost; ++i) {
@@ -505,10 +520,13 @@ void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool ato
       if (s > 1 && ((!in_ws && !atomics) || tiles * s > 512 * t.together)) break;
       const int kt = (nk + s - 1) / s;
       if (s > 1 && (nk + kt - 1) / kt != s) continue;   // an empty split
-      const double wgs = (double)tiles * s, per_cu = std::ceil(wgs / 256.0), rounds = std::ceil(per_cu / t.together);
-      const double lone = t.lone_few + (t.lone_all - t.lone_few) * std::min(1.0, wgs / 256.0);
-      double us = kt * std::max(rounds * lone, per_cu > 1 ? per_cu * t.busy : 0.0) + rounds * t.rest;
-      if (s > 1) us += in_ws ? (accum ? 4.3 + (double)s * g.M * g.N * 8.0 / 6.5e6 : (ln ? 1.0 : 6.0) + (double)s * g.M * g.N * 8.0 / 4.0e6) : (double)s * g.M * g.N * 4.0e-6;
+      if (t.v == 5 && small_tile_two_stages(g.M, g.N, g.K, 1, s) != (t.together == 4)) continue;   // the other row's
+      const double extra = s > 1 ? t.f32 : element ? t.element : out_f32 && (g.epi & EPI_ACCUM) ? t.accum : second ? t.second : out_f32 ? t.f32 : 0.0;
+      const long long wgs = tiles * s, per_cu = (wgs + 255) / 256, rounds = (per_cu + t.together - 1) / t.together;
+      const double lone = t.lone_few + (t.lone_all - t.lone_few) * std::min(1.0, (double)wgs / 256.0);
+      double us = kt * std::max(rounds * lone, per_cu > 1 ? per_cu * t.busy : 0.0) + rounds * (t.rest + extra);
+      if (s > 1 && !in_ws) us += (double)s * g.M * g.N * 2.9e-6;
+      else if (s > 1) us += accum ? 2.6 + s * 0.02 + (double)s * g.M * g.N * 8.0 / 5.1e6 : (ln ? 1.0 : 2.2) + s * 0.21 + (double)s * g.M * g.N * 8.0 / 7.6e6;
       if (us < best) { best = us; *variant = t.v; *splits = s; }
     }
   }
@@ -517,7 +535,7 @@ void choose_tile_within(const GemmArgs& g, bool accum, size_t ws_elems, bool ato
 void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant, int* splits, bool ln = false) {
   if (g.a_kc != g.b_kc || g.nbatch != 1 || g.m_dev || g.k_dev) return pick_tile(g, out_f32, variant, splits);
   if (!(out_f32 && g.epi == EPI_ACCUM)) {
-    choose_tile_within(g, false, ws_elems, false, variant, splits, ln);
+    choose_tile_within(g, out_f32, false, ws_elems, false, variant, splits, ln);
     // (a caller's buffer of column sums may have room for the wider wave tiles that the rule by size takes, and no more)
     if ((g.epi & EPI_COLSUM) && g.colsum_rows > 0 && (g.M + kTiles[*variant].wm - 1) / kTiles[*variant].wm > g.colsum_rows) pick_tile(g, out_f32, variant, splits);
     return;
@@ -525,11 +543,11 @@ void choose_tile(const GemmArgs& g, bool out_f32, size_t ws_elems, int* variant,
   // An accumulating launch splits through the workspace where two slices fit (the layer's do, if it wants any: the sums then
   // have a fixed order), else with atomics where the rule by size would: a small context holds next to nothing, and a row
   // pitch may not allow 16-byte access.
-  choose_tile_within(g, true, ws_elems, false, variant, splits);
+  choose_tile_within(g, true, true, ws_elems, false, variant, splits);
   if (*splits > 1 || (split_sum_ok(g) && (size_t)2 * g.M * g.N <= ws_elems)) return;
   int v, by_size;
   pick_tile(g, true, &v, &by_size);
-  if (by_size > 1) choose_tile_within(g, true, ws_elems, true, variant, splits);
+  if (by_size > 1) choose_tile_within(g, true, true, ws_elems, true, variant, splits);
 }
 
 // whether gemm() will run this launch on the direct-to-LDS kernel, the one that honours EPI_COLSUM; otherwise the

@@ -20,14 +20,15 @@
 constexpr int kNumGemmVariants = 9;
 
 // 64 x 64 tiles: whether two LDS stages are faster than three, which hide the way to memory but of which three workgroups and
-// not four share a compute unit.  They are with less than six k-tiles (bias and residual, two and three stages: 7000 x 512 x 128
-// 7.5 and 8.8 us, 4096 x 1024 x 256 9.0 and 10.2, 16384 x 1280 x 320 35.9 and 37.8; 8192 x 768 x 768 21.6 and 19.6, 5000 x 1024 x
-// 1024 24.2 and 20.5), and where the launch fits the chip with four workgroups per unit but not with three (4096 x 1024 x 1024
-// 16.6 and 18.1, 7000 x 512 x 512 10.4 and 11.7; with 32 k-tiles no difference).
+// not four share a compute unit.  They are with less than six k-tiles where units have more than one workgroup (bias and residual,
+// two and three stages: 7000 x 512 x 128 7.5 and 8.8 us, 4096 x 1024 x 256 9.0 and 10.2, 16384 x 1280 x 320 35.9 and 37.8; but
+// 8192 x 768 x 768 21.6 and 19.6, 5000 x 1024 x 1024 24.2 and 20.5, and a layer of 256 columns forward, 64 tokens, 33.0 and 32.1),
+// and where the launch fits the chip with four workgroups per unit but not with three (4096 x 1024 x 1024 16.6 and 18.1,
+// 7000 x 512 x 512 10.4 and 11.7; with 32 k-tiles no difference).
 inline bool small_tile_two_stages(int M, int N, int K, int nbatch, int splits) {
   const int k_tiles = ((K + 63) / 64 + splits - 1) / splits;
   const long long blocks = (long long)((M + 63) / 64) * ((N + 63) / 64) * splits * nbatch;
-  return k_tiles < 6 || (k_tiles < 24 && blocks > 3 * 256 && blocks <= 4 * 256);
+  return blocks > 256 && (k_tiles < 6 || (k_tiles < 24 && blocks > 3 * 256 && blocks <= 4 * 256));
 }
 
 // launches variant `index` (layouts and output type taken from the arguments)

@@ -485,7 +485,7 @@ int variant_for_layout(int v, const GemmArgs& g) {
 // against 41.6.  Both operands K-strided it gains nothing (66.4 against 66.7 us at 1024 x 4096 x 4096: bound by LDS reads).
 // The 64 x 64 tile (variant 5) has three stages or two by small_tile_two_stages, one row for each.
 struct TileCost { int v; double busy, lone_few, lone_all, rest; int together; double second, f32, accum, element; };
-constexpr TileCost kCostKC[] = {{5, 0.212, 0.211, 0.231, 3.632, 3, 0.36, 0.50, 0, 3.57}, {5, 0.226, 0.400, 0.500, 4.399, 4, 0, 0, 0, 2.94},
+constexpr TileCost kCostKC[] = {{5, 0.212, 0.211, 0.231, 3.632, 3, 0.36, 0.50, 0, 3.57}, {5, 0.270, 0.210, 0.210, 3.700, 4, 0, 0, 0, 2.94},
                                 {7, 0.565, 0.423, 0.751, 4.486, 2, 1.00, 0.99, 0, 15.65}, {4, 0.582, 0.401, 0.582, 5.751, 1, 0.67, 0, 0, 9.39},
                                 {8, 0.914, 0.525, 0.914, 6.218, 1, 1.00, 2.72, 0, 17.11}, {6, 1.270, 0.559, 1.270, 8.117, 1, 3.53, 1.60, 0, 14.59}};
 // ... where the launch adds to C in fp32
@@ -526,7 +526,7 @@ void choose_tile_within(const GemmArgs& g, bool out_f32, bool accum, size_t ws_e
       const double lone = t.lone_few + (t.lone_all - t.lone_few) * std::min(1.0, (double)wgs / 256.0);
       double us = kt * std::max(rounds * lone, per_cu > 1 ? per_cu * t.busy : 0.0) + rounds * (t.rest + extra);
       if (s > 1 && !in_ws) us += (double)s * g.M * g.N * 2.9e-6;
-      else if (s > 1) us += accum ? 2.6 + s * 0.02 + (double)s * g.M * g.N * 8.0 / 5.1e6 : (ln ? 1.0 : 2.2) + s * 0.21 + (double)s * g.M * g.N * 8.0 / 7.6e6;
+      else if (s > 1) us += accum ? 2.6 + s * 0.02 + (double)s * g.M * g.N * 8.0 / 5.1e6 : (ln ? 1.0 + s * 0.05 : 2.2 + s * 0.21) + (double)s * g.M * g.N * 8.0 / 7.6e6;
       if (us < best) { best = us; *variant = t.v; *splits = s; }
     }
   }

@@ -1430,25 +1430,52 @@ def test_gemm_two_wave_group_tile_rows_far_apart(ctx):
 @pytest.mark.parametrize("stats", [False, True])
 @pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp16"])
 @pytest.mark.parametrize("hidden,heads", [(8, 1), (256, 4), (520, 1), (1024, 16), (1032, 3), (2048, 32), (2056, 1)])
-def test_layer_few_rows_layernorm_adds_the_splits(hidden, heads, dtype, stats):
-    # 16 tokens: the products in front of both LayerNorms are split over K and the LayerNorm kernel adds the splits up (one
-    # to four waves per row, partly filled ones; from 2056 columns on the two kernels run one after the other)
+def test_layer_few_rows_layernorm_adds_the_splits(monkeypatch, hidden, heads, dtype, stats):
+    # 16 tokens: products in front of the LayerNorms are split over K and the LayerNorm kernel adds the splits up (one to four
+    # waves per row, partly filled ones); at 8 columns there is nothing to split, and from 2056 columns on the two kernels run
+    # one after the other.  The recorded traffic of the LayerNorms says which kernel ran: 4 bytes per element and split more
     w = S.Workload("few_rows", 1, hidden, heads, 4 * hidden, 8, 50, 1, 2, dtype, 1.0, 900 + hidden)
     _assert_errs(_layer_case(w, stats=stats, dy_scale=256.0 if dtype == "fp16" else 1.0), TOL[dtype])
+    cfg = P.make_config(hidden, heads, 4 * hidden, 8, 1, 2, dtype, 1e-12, 0)
+    dt = {"fp32": torch.float32, "fp16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    splits = {}
+    for fused in (True, False):
+        if not fused:
+            monkeypatch.setenv("L2L_SPLIT_ATOMICS", "1")
+        c = P.Context(cfg)
+        try:
+            host = torch.zeros(P.lib().l2l_layer_packed_elems(cfg), dtype=dt).pin_memory()
+            c.param_stage(0, host, 0)
+            x = torch.ones((2, 8, hidden), device="cuda", dtype=dt)
+            y = torch.empty_like(x)
+            c.sync()
+            c.profile(1)
+            c.layer_fwd(0, 0, x, y)
+            c.sync()
+            traffic = c.profile_read()["rowwise"]["bytes"]
+            c.profile(0)
+        finally:
+            c.close()
+        splits[fused] = (traffic / (16 * hidden) - 4 * x.element_size()) / 4
+    assert splits[False] == 0
+    assert splits[True] == 0 if hidden in (8, 2056) else splits[True] >= 2, splits
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 @pytest.mark.parametrize("K", [8, 64, 72, 136, 200, 264, 320, 328, 384, 392, 456, 520, 1032])
 def test_gemm_small_tile_three_stages_k_tile_counts(ctx, K, dtype):
-    # 64 x 64 tiles, ragged edges, both output types and epilogue paths: one to five k-tiles through two LDS stages, six to
-    # seventeen through three
+    # 64 x 64 tiles, one to seventeen k-tiles through three LDS stages, ragged edges, both output types and epilogue paths
     assert _gemm_case(ctx, dtype, 105, 1, 1, 200, 136, K, bias=True, resid=True, pad=8) < OUT16[dtype]
     assert _gemm_case(ctx, dtype, 105, 1, 1, 65, 72, K, bias=True, gelu=True, alpha=0.5, pad=3) < OUT16[dtype]
     assert _gemm_case(ctx, dtype, 105, 1, 1, 200, 136, K, out_f32=True, pad=8) < 2e-6
 
 
-@pytest.mark.parametrize("M,N", [(1536, 2048), (1537, 2048), (2048, 2048), (2049, 2048)])
+@pytest.mark.parametrize("M,N", [(1024, 1024), (1025, 1024), (1536, 2048), (1537, 2048), (2048, 2048), (2049, 2048)])
 def test_gemm_small_tile_stages_by_workgroups(ctx, M, N):
-    # 64 x 64 tiles with six and seven k-tiles: 768 workgroups and 1056 go through three LDS stages, 800 and 1024 through two
+    # 64 x 64 tiles with one to seven k-tiles: 256 workgroups through three LDS stages, 272 and more through two up to five
+    # k-tiles; with six and seven 768 workgroups and 1056 through three, 800 and 1024 through two
+    for K in (8, 72, 136, 256, 320):
+        _gemm_ex_case(ctx, "bf16", M, N, K, impl=105, seed=M + K, **EPILOGUES[9])
     _gemm_ex_case(ctx, "bf16", M, N, 384, impl=105, seed=M, **EPILOGUES[9])
     _gemm_ex_case(ctx, "fp16", M, N, 392, impl=105, seed=M, **EPILOGUES[67])
+    _gemm_ex_case(ctx, "fp16", M, N, 200, impl=105, seed=M, out_f32=True, accumulate=True)

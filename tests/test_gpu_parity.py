@@ -170,7 +170,7 @@ EPILOGUES = {0: dict(), 1: dict(bias=True), 9: dict(bias=True, resid=True), 3: d
 
 
 def _gemm_ex_case(ctx, dtype, M, N, K, bias=False, resid=False, gelu=False, gelugrad=False, colsum=False, a_kc=1, b_kc=1,
-                  out_f32=False, accumulate=False, seed=0, keepgrad=False, mulaux=False, impl=0, alpha=1.0):
+                  out_f32=False, accumulate=False, seed=0, keepgrad=False, mulaux=False, impl=0, alpha=1.0, colsum_per_rows=None):
     """One l2l_op_gemm_ex launch (impl 0: library's choice of kernel) checked ELEMENT BY ELEMENT against
     epilogue(alpha rounded(A) @ rounded(B)) in fp64.  Bounds per element: an fp32 output may differ by the fp32
     accumulation error (2e-6 of the row-times-column magnitude); a 16-bit output additionally by one rounding to the
@@ -243,6 +243,7 @@ def _gemm_ex_case(ctx, dtype, M, N, K, bias=False, resid=False, gelu=False, gelu
         assert np.all(np.abs(au[:, :N] - kept) <= slack + 0.5 * ULP[dtype] * 1.001 * np.abs(kept))
     if colsum:     # partial sums of the values before their rounding to the output format; rows beyond `used` untouched
         assert 0 < used <= cs_rows
+        assert colsum_per_rows is None or used == (M + colsum_per_rows - 1) // colsum_per_rows
         cs = to_host(csd)
         assert np.all(cs[used:] == 12345.0), "column-sum rows beyond the reported count were written"
         col_tol = tol.sum(axis=0) + 1e-6 * np.abs(ref).sum(axis=0)
@@ -253,11 +254,14 @@ def _gemm_ex_case(ctx, dtype, M, N, K, bias=False, resid=False, gelu=False, gelu
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 @pytest.mark.parametrize("epi", sorted(EPILOGUES))
 def test_gemm_every_compiled_epilogue_elementwise(ctx, dtype, epi):
-    # 256 x 256 tiles with 16-bit output and both operands K-contiguous: the instantiations with the epilogue flags
-    # compiled in (flag sets 0, 1, 9, 3, 67, 128, 160, 8) and, for 4, 36 and 32, the one that reads them at run time; two
-    # tile rows and columns with ragged edges, K with a tail
+    # 16-bit output and both operands K-contiguous, two tile rows and columns of 256 x 256 with ragged edges, K with a tail: the
+    # instantiations with the epilogue flags compiled in (flag sets 0, 1, 9, 3, 67, 128, 160, 8) and, for 4, 36 and 32, the one
+    # that reads them at run time; on the tile that the library chooses (128 x 128 or 64 x 64 here), and on 256 x 256 ones.
+    # Column sums come with the library's choice only: tests of those on 256 x 256 tiles take shapes that it gives them
     errs = _gemm_ex_case(ctx, dtype, 392, 520, 264, seed=epi, **EPILOGUES[epi])
     _report(f"gemm_ex[{dtype}-epi{epi}]", {"C": errs[0], "max:C": errs[1]})
+    if not EPILOGUES[epi].get("colsum"):
+        _gemm_ex_case(ctx, dtype, 392, 520, 264, seed=epi, impl=106, **EPILOGUES[epi])
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
@@ -278,22 +282,32 @@ def test_gemm_small_launches_elementwise(monkeypatch, M, N, K, dtype):
         c.close()
 
 
-@pytest.mark.parametrize("K", [136, 1032])
-@pytest.mark.parametrize("epi", [9, 67, 160])
+@pytest.mark.parametrize("K", [64, 128, 136, 1032])
+@pytest.mark.parametrize("epi", [9, 67, 128, 4])
 def test_gemm_resident_tile_walk_elementwise(ctx, K, epi):
     # 19 x 18 = 342 tiles of 256 x 256, more than the chip has compute units: workgroups stay resident and walk the tile
-    # order, fetching the next tile's first k-tile under the epilogue of the current one; ragged M, N and K.  K = 136
-    # leaves that prefetch as most of a tile's loads, K = 1032 is the layer's depth plus a tail
-    errs = _gemm_ex_case(ctx, "bf16", 4616, 4360, K, seed=K + epi, **EPILOGUES[epi])
+    # order, fetching the next tile's first k-tiles under the epilogue of the current one, whose second operand is requested
+    # between them and the stores; ragged M, N and K.  One, two and three k-tiles leave that prefetch as all or most of a
+    # tile's loads, K = 1032 is the layer's depth plus a tail
+    errs = _gemm_ex_case(ctx, "bf16", 4616, 4360, K, seed=K + epi, impl=106, **EPILOGUES[epi])
     _report(f"gemm_resident[K{K}-epi{epi}]", {"C": errs[0], "max:C": errs[1]})
+
+
+@pytest.mark.parametrize("epi", [160, 36, 32])
+@pytest.mark.parametrize("M,N,K", [(5000, 8200, 72), (5000, 8200, 136), (4616, 4360, 1032)])
+def test_gemm_resident_tile_walk_column_sums(ctx, M, N, K, epi):
+    # the same walk with column sums (times the kept activation's factor, times GELU', alone), at shapes for which the library
+    # takes 256 x 256 tiles: theirs are the only sums that come per 128 rows
+    _gemm_ex_case(ctx, "bf16", M, N, K, seed=K + epi, colsum_per_rows=128, **EPILOGUES[epi])
 
 
 def test_gemm_resident_tile_walk_other_layouts_elementwise(ctx):
     # the same walk for the dW layout (both operands K-strided, fp32 accumulate into C: 342 tiles, no K split) and for
     # fp16 operands
-    _gemm_ex_case(ctx, "bf16", 4616, 4360, 520, a_kc=0, b_kc=0, out_f32=True, accumulate=True, seed=5)
-    _gemm_ex_case(ctx, "fp16", 4616, 4360, 264, seed=6, **EPILOGUES[9])
-    _gemm_ex_case(ctx, "bf16", 4616, 4360, 264, a_kc=1, b_kc=0, out_f32=True, seed=7)
+    for K in (72, 136, 520):
+        _gemm_ex_case(ctx, "bf16", 4616, 4360, K, a_kc=0, b_kc=0, out_f32=True, accumulate=True, seed=5, impl=106)
+    _gemm_ex_case(ctx, "fp16", 4616, 4360, 264, seed=6, impl=106, **EPILOGUES[9])
+    _gemm_ex_case(ctx, "bf16", 4616, 4360, 264, a_kc=1, b_kc=0, out_f32=True, seed=7, impl=106)
 
 
 def test_gemm_column_sums_row_count_at_wave_tile_edges(ctx):
@@ -1404,26 +1418,74 @@ def test_gemm_two_wave_group_tile_general_epilogues_elementwise(ctx, dtype, M, N
             _gemm_ex_case(ctx, dtype, M, N, K, out_f32=True, **f32, **kw)
 
 
-def test_gemm_two_wave_group_tile_rows_far_apart(ctx):
-    # rows of C and of the residual 2^22 + 8 elements apart: a wave's part of them is more than a buffer descriptor covers,
-    # and the epilogue goes through pointers (16-bit with bias and residual; fp32 accumulating)
-    M, N, K, ld = 130, 264, 136, 2 ** 22 + 8
+FAR = 2 ** 22 + 8      # elements from row to row: a wave's 128 rows are more than a buffer descriptor covers
+
+
+def _far(M, fill, dtype=torch.bfloat16):
+    return torch.full((M, FAR), fill, device="cuda", dtype=dtype)
+
+
+@pytest.mark.parametrize("flags", ["bias and residual", "GELU and its derivative", "factor", "factor and column sums"])
+def test_gemm_two_wave_group_tile_rows_far_apart(ctx, flags):
+    # 256 x 256 tiles with rows of C and of what goes with it far apart: the epilogue goes through pointers.  Per element: the
+    # fp32 accumulation (2e-6 of the sum of magnitudes), one rounding to bf16, GELU's polynomials as in _gemm_ex_case
+    M, N, K = (250, 65528, 136) if "column" in flags else (130, 264, 136)      # (256 tiles in one row: the library's own choice)
     g = torch.Generator(device="cuda").manual_seed(3)
     A, Bm = (torch.randn(s, device="cuda", generator=g).to(torch.bfloat16) for s in ((M, K), (N, K)))
     bias = torch.randn(N, device="cuda", generator=g).to(torch.bfloat16)
-    ref = A.double() @ Bm.double().t()
-    out, res = (torch.full((M, ld), 7.0, device="cuda", dtype=torch.bfloat16) for _ in range(2))
-    res[:, :N] = torch.randn((M, N), device="cuda", generator=g).to(torch.bfloat16)
-    ctx.op_gemm(P.L2L_BF16, False, 1, 1, M, N, K, A, K, Bm, K, out, ld, bias=bias, resid=res, impl=106)
-    want = ref + bias.double() + res[:, :N].double()
-    # fp32 accumulation (2e-6 of the sum of magnitudes) and one rounding to bf16
-    tol = 2e-6 * (A.double().abs() @ Bm.double().abs().t()) + 0.5 * ULP["bf16"] * 1.001 * want.abs()
-    assert bool(((out[:, :N].double() - want).abs() <= tol).all())
-    assert bool((out[:, N:N + 64] == 7).all()) and bool((out[:, -64:] == 7).all())
-    del out, res
-    acc = torch.full((M // 8, ld), 7.0, device="cuda")
-    ctx.op_gemm(P.L2L_BF16, True, 1, 1, M // 8, N, K, A, K, Bm, K, acc, ld, accumulate=True, impl=106)
-    assert bool(((acc[:, :N].double() - ref[:M // 8] - 7).abs() <= tol[:M // 8] + 1e-6).all())
+    want, mag = A.double() @ Bm.double().t(), 2e-6 * (A.double().abs() @ Bm.double().abs().t())
+    out = _far(M, 7.0)
+    rounding = 0.5 * ULP["bf16"] * 1.001
+
+    def check(got, want, tol):
+        assert bool(((got[:, :N].double() - want).abs() <= tol).all())
+        assert bool((got[:, N:N + 64] == 7).all()) and bool((got[:, -64:] == 7).all())
+
+    if flags == "bias and residual":
+        res = _far(M, 7.0)
+        res[:, :N] = torch.randn((M, N), device="cuda", generator=g).to(torch.bfloat16)
+        ctx.op_gemm_ex(P.L2L_BF16, False, 1, 1, M, N, K, A, K, Bm, K, out, FAR, bias=bias, resid=res, ldr=FAR, impl=106)
+        want = want + bias.double() + res[:, :N].double()
+        check(out, want, mag + rounding * want.abs())
+    elif flags == "GELU and its derivative":
+        kept = _far(M, 7.0)
+        ctx.op_gemm_ex(P.L2L_BF16, False, 1, 1, M, N, K, A, K, Bm, K, out, FAR, bias=bias, epi=B.EPI_GELU | B.EPI_KEEPGRAD, aux_out=kept, ldaux=FAR, impl=106)
+        u = want + bias.double()
+        phi = 0.5 * (1 + torch.erf(u / math.sqrt(2)))
+        grad = phi + u * torch.exp(-u * u / 2) / math.sqrt(2 * math.pi)
+        check(out, u * phi, 1.2 * mag + 5e-5 * u.abs() + rounding * (u * phi).abs())      # (|gelu'| <= 1.13)
+        check(kept, grad, 1.2 * mag + 5e-5 + rounding * grad.abs())
+    else:
+        fac = _far(M, 7.0)
+        fac[:, :N] = torch.randn((M, N), device="cuda", generator=g).to(torch.bfloat16)
+        kw = dict(epi=B.EPI_MULAUX, aux=fac, ldaux=FAR, impl=106)
+        if "column" in flags:
+            rows = (M + 63) // 64
+            cs = torch.full((rows + 1, N), 12345.0, device="cuda")
+            kw = dict(epi=B.EPI_MULAUX | B.EPI_COLSUM, aux=fac, ldaux=FAR, colsum=cs, colsum_rows=rows)
+        used = ctx.op_gemm_ex(P.L2L_BF16, False, 1, 1, M, N, K, A, K, Bm, K, out, FAR, **kw)
+        f = fac[:, :N].double()
+        want, mag = want * f, mag * f.abs()
+        check(out, want, mag + rounding * want.abs())
+        if "column" in flags:
+            assert used == (M + 127) // 128          # (a row of sums per 128 rows: 256 x 256 tiles)
+            assert bool((cs[used:] == 12345.0).all())
+            assert bool(((cs[:used].double().sum(0) - want.sum(0)).abs() <= mag.sum(0) + 1e-6 * want.abs().sum(0)).all())
+
+
+@pytest.mark.parametrize("kc", [1, 0])
+def test_gemm_two_wave_group_tile_adds_to_rows_far_apart(ctx, kc):
+    # fp32 sums into rows that lie far apart, operands of either layout: the fp32 accumulation and one fp32 addition to the 7
+    # that C holds
+    M, N, K = 16, 264, 136
+    g = torch.Generator(device="cuda").manual_seed(4)
+    A, Bm = (torch.randn(s, device="cuda", generator=g).to(torch.bfloat16) for s in ((M, K), (N, K)))
+    acc = _far(M, 7.0, torch.float32)
+    Ad, Bd = (A, Bm) if kc else (A.t().contiguous(), Bm.t().contiguous())
+    ctx.op_gemm(P.L2L_BF16, True, kc, kc, M, N, K, Ad, K if kc else M, Bd, K if kc else N, acc, FAR, accumulate=True, impl=106)
+    want = A.double() @ Bm.double().t() + 7
+    tol = 2e-6 * (A.double().abs() @ Bm.double().abs().t() + 7)
+    assert bool(((acc[:, :N].double() - want).abs() <= tol).all())
     assert bool((acc[:, N:N + 64] == 7).all()) and bool((acc[:, -64:] == 7).all())
 
 

@@ -672,8 +672,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   if (kt0 >= kt1) return;
 
   // A workgroup takes tiles blockIdx.x, blockIdx.x + gridDim.x, ...: launched with one workgroup per tile it runs
-  // once, launched with one workgroup per CU it stays resident and walks its share of the tile order, which
-  // saves the dispatch of a 512-thread, 128 KB workgroup per tile.
+  // once, launched with one workgroup per CU (256 x 128 tiles) it stays resident and walks its share of the tile order,
+  // which saves the dispatch of a 512-thread, 144 KB workgroup per tile.
   const int z = blockIdx.z, zo = z / g.zdiv, zi = z % g.zdiv;
   const uint32_t lda = (uint32_t)g.lda, ldb = (uint32_t)g.ldb;
   // buffer descriptors of the operand panels of the tile at (m0, n0)
@@ -706,9 +706,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   // window in which their stage is free: LS0 of them right after the barrier (last k16-step of tile t), then up to
   // LS1, LS2, LS3 in total by the first three k16-steps of tile t + 1; the barrier of tile t + 1 needs them landed.
   constexpr int NLD = DA::PER + DB::PER;
-  // Measured (on a 256 x 256 tile, 8 loads per wave, which gemm_pp.h has taken over since): K-contiguous x K-contiguous gains 6-8 % with 2 + 3 + 3 + 0 against all
-  // 8 at once (per k-tile: 3250 -> 2700 clocks, of which load issue 920 -> 90 and barrier wait 620 -> 310);
-  // K-strided operands, whose fragment reads already load the LDS pipe more, do best with the burst.
+  // The shares were measured with 256 x 256 tiles, 8 loads per wave, which run on gemm_mfma_pp_kernel now, and not again on the
+  // tiles left here: K-contiguous x K-contiguous gained 6-8 % with 2 + 3 + 3 + 0 against all 8 at once (per k-tile: 3250 -> 2700
+  // clocks, of which load issue 920 -> 90 and barrier wait 620 -> 310); K-strided operands, whose fragment reads already load
+  // the LDS pipe more, did best with the burst.
   constexpr int SPLIT0 = (AKC && BKC) ? 2 : (AKC || BKC) ? 4 : 8, SPLIT1 = (AKC && BKC) ? 5 : 8, SPLIT2 = 8;   // cumulative eighths
   constexpr int LS0 = (NLD * SPLIT0 + 7) / 8, LS1 = (NLD * SPLIT1 + 7) / 8, LS2 = (NLD * SPLIT2 + 7) / 8;
   const auto load_ab = [&](auto i0c, auto i1c, int kbase, char* stage) {
@@ -795,11 +796,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
   constexpr int CPR = WN / 8, RPP = 64 / CPR, PASSES = 32 / RPP;
   const int c8 = (lane % CPR) * 8, prow = lane / CPR;
   const int ncol = n0 + wn * WN + c8;
-  // fp32 results without a 16-bit operand to read beside them: a lane's 8 columns are two groups of 4, half a wave tile
-  // apart, so that each 16-byte store of a wave covers whole 128-byte lines (8 adjacent columns per lane are two stores
-  // that each touch half of every line: logits of 4915 x 30522
-  // 411 -> 378 us, a dW over 32768 tokens 318 -> 304)
-  constexpr bool F4 = sizeof(TC) == 4 && (EPI == 0 || EPI == EPI_BIAS);
+  // fp32 results stored as they are (K splits' partial sums, a first dW): a lane's 8 columns are two groups of 4, half a
+  // wave tile apart, so that each 16-byte store of a wave covers whole 128-byte lines (8 adjacent columns per lane are two
+  // stores that each touch half of every line: a dW over 32768 tokens 318 -> 304 us, measured with 256 x 256 tiles)
+  constexpr bool F4 = sizeof(TC) == 4 && EPI == 0;
   const int c4 = (lane % CPR) * 4;
   float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float csum8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // EPI_COLSUM: this lane's share of its 8 columns' sums
@@ -827,15 +827,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
     }
   };
   if (vec_ok && !atomic) {
-    if constexpr (F4) {
-      if (epi & EPI_BIAS) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int n = n0 + wn * WN + c4 + (e & 3) + (e >> 2) * (WN / 2);
-          if (n < N) bias8[e] = to_f32(((const E*)g.bias)[n]);
-        }
-      }
-    } else if ((epi & EPI_BIAS) && ncol < N) load8((const E*)g.bias + ncol, bias8);
+    if ((epi & EPI_BIAS) && ncol < N) load8((const E*)g.bias + ncol, bias8);
     static_for<0, PD - 1>([&](auto qc) {
       constexpr int q = decltype(qc)::value;
       if constexpr (q < FM * PASSES) fetch(q / PASSES, q % PASSES, pre[q]);
@@ -889,9 +881,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_mfma_dlds_ker
           static_for<0, 2>([&](auto hc) {
             constexpr int hf = decltype(hc)::value;
             if (m < M && ncol0 + c4 + hf * (WN / 2) < N) {
-              f32x4 v = *(const f32x4*)(strip + (p * RPP + prow) * EP_PITCH + c4 + hf * (WN / 2));
-              if (epi & EPI_BIAS) v += f32x4{bias8[4 * hf], bias8[4 * hf + 1], bias8[4 * hf + 2], bias8[4 * hf + 3]};
-              *(f32x4*)(cp + hf * (WN / 2)) = v;
+              *(f32x4*)(cp + hf * (WN / 2)) = *(const f32x4*)(strip + (p * RPP + prow) * EP_PITCH + c4 + hf * (WN / 2));
             }
           });
           return;

@@ -125,7 +125,7 @@ void launch_direct(const GemmArgs& g, hipStream_t s, int splits) {
         return;
       }
     }
-    if constexpr (BM == 256 && BN == 256)
+    if constexpr (NST == PP)
       if (g.alpha == 1.0f && g.a_kc && g.b_kc && g.epi == EPI_BIAS) { launch_direct_one<BM, BN, WM, WN, true, true, TC, E, NST, EPI_BIAS>(g, s, splits); return; }
   }
   if constexpr (BM < 128) {   // built for K-contiguous operands only: callers see to it

@@ -19,7 +19,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0       # MI355X dense bf16 MFMA
 # HBM bytes per layer-GEMM launch of the headline workload, from counters collected offline (see roofline.traffic_source)
-HBM_TRAFFIC_PER_LAUNCH = 553.9e6
+HBM_TRAFFIC_PER_LAUNCH = 637.1e6
 
 
 def cpu_baseline(w):
@@ -239,7 +239,7 @@ def main():
                      # measured on the headline workload only
                      "traffic": HBM_TRAFFIC_PER_LAUNCH if (a.config == 2 and not a.layers and not a.group and not a.ubatches and not a.dtype and not a.classes and a.grad_dtype == "fp32") else None,
                      "traffic_source": "offline: two rocprofv3 --pmc runs of this command (FETCH_SIZE, WRITE_SIZE), profiles/bench_bert_large_gemm_hbm_traffic.md; not measured in this run",
-                     "kernel": "gemm_mfma_dlds_kernel / gemm_mfma_kernel: the layer's dense GEMMs (QKV, out-proj, FFN1, FFN2; forward, recompute, dX, dW)",
+                     "kernel": "gemm_mfma_pp_kernel (256 x 256 tiles: every layer GEMM of the headline workload), gemm_mfma_dlds_kernel (smaller tiles), gemm_f32_kernel (fp32): the layer's dense GEMMs (QKV, out-proj, FFN1, FFN2; forward, recompute, dX, dW)",
                      "gemm_ms_per_step": g["ms"] / a.steps, "launches_per_step": g["launches"] / a.steps,
                      "avg_launch_us": 1e3 * g["ms"] / max(g["launches"], 1),
                      "flops_per_launch": g["flops"] / max(g["launches"], 1)},
